@@ -16,11 +16,15 @@ LIB = os.path.join(HERE, "libces.so")
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 
 SOURCES = ["kernels.hip", "kernels_angular.hip", "kernels_radial.hip", "kernels_scf.hip",
-           "kernels_mlp.hip", "kernels_block.hip", "kernels_kb.hip", "kernels_lobpcg.hip", "noalloc.hip", "capi.cpp", "lobpcg.cpp", "scf.cpp", "learned.cpp", "setup_tables.cpp"]
+           "kernels_phi.hip", "kernels_mlp.hip", "kernels_block.hip", "kernels_kb.hip", "kernels_lobpcg.hip", "noalloc.hip", "capi.cpp", "lobpcg.cpp", "scf.cpp", "learned.cpp", "setup_tables.cpp"]
 
-# Device code: gfx950 only; packed-FP32 instructions disabled.
+# Device code: gfx950 only; packed-FP32 instructions disabled.  MFMA results
+# stay in VGPRs: by itself the compiler puts them in AGPRs and copies them out
+# and back around every loop that also reads them (kernels_angular.hip: 2,789
+# copy instructions against 650; a register-only FP64 MFMA loop runs at 49
+# TFLOP/s with the copies and 78 without).
 DEVICE_FLAGS = ["--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang",
-                "-packed-fp32-ops"]
+                "-packed-fp32-ops", "-mllvm", "-amdgpu-mfma-vgpr-form=1"]
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-result",
           f"-I{os.path.join(ROOT, 'include')}", f"-I{ROCM}/include"]
 
