@@ -169,6 +169,41 @@ void fill_tables(const Basis& b, std::vector<T>& Rinv, std::vector<T>& Rfwd,
       }
 }
 
+// Operand tables of the phi transforms (kernels_phi.hip), lane = 16 kk + l16
+// of a 16 x 4 operand; m = row of the half, plus 1 in the sine half:
+//   analysis  [t][e][half][m tile][lane]: (2 pi / n) trig(m phi_{1+q}), m =
+//             16 tile + l16, pair q = 16 t + 4 kk + e < n / 2 (half weight at
+//             the self-mirrored point n / 2)
+//   synthesis [p tile][t][half][lane]: trig(m phi_p), m = 4 t + kk, p = 16
+//             tile + l16 <= n / 2
+// and zero outside.
+void fill_trig_tables(const Basis& b, const std::vector<double>& cs, std::vector<double>& ta,
+                      std::vector<double>& ts) {
+  const int L = b.L, n = b.n_phi, npair = n / 2, LT = (L + 15) / 16, nk = trig_kt(L);
+  const int nt = (npair + 15) / 16, npt = npair / 16 + 1;
+  auto trig = [&](int half, int m, int p) {
+    return cs[size_t(half) * n + static_cast<int>(int64_t(m) * p % n)];
+  };
+  ta.assign(std::max<size_t>(size_t(nt) * 4 * 2 * LT * 64, 1), 0.0);
+  for (int t = 0; t < nt; ++t)
+    for (int e = 0; e < 4; ++e)
+      for (int half = 0; half < 2; ++half)
+        for (int row = 0; row < L - half; ++row)
+          for (int kk = 0; kk < 4; ++kk) {
+            const int q = 16 * t + 4 * kk + e;
+            if (q >= npair) continue;
+            const double w = 2.0 * M_PI / n * (2 * (1 + q) == n ? 0.5 : 1.0);
+            ta[((size_t(t) * 4 + e) * 2 + half) * LT * 64 + (row / 16) * 64 + 16 * kk + row % 16] =
+                w * trig(half, row + half, 1 + q);
+          }
+  ts.assign(size_t(npt) * nk * 2 * 64, 0.0);
+  for (int p = 0; p <= npair; ++p)
+    for (int half = 0; half < 2; ++half)
+      for (int row = 0; row < L - half; ++row)
+        ts[((size_t(p / 16) * nk + row / 4) * 2 + half) * 64 + 16 * (row % 4) + p % 16] =
+            trig(half, row + half, p);
+}
+
 // Upload device tables once (on the device current at first use).
 ces_status ensure_device(Basis& b) {
   std::lock_guard<std::mutex> lock(b.dev_mu);
@@ -187,6 +222,9 @@ ces_status ensure_device(Basis& b) {
     cs[u] = std::cos(2.0 * M_PI * u / b.n_phi);
     cs[b.n_phi + u] = std::sin(2.0 * M_PI * u / b.n_phi);
   }
+  std::vector<double> trig_a, trig_s;
+  fill_trig_tables(b, cs, trig_a, trig_s);
+  const std::vector<float> trig_s32(trig_s.begin(), trig_s.end());
   // Hartree radial table (Section 2.3.1): the Laplace-expansion radial
   // integral zeta_ln(r) of R_ln in closed form, with k = b_ln / R,
   //   (4 pi / (2l+1)) zeta_ln(r) = (4 pi / k^2) R_ln(r)
@@ -235,6 +273,9 @@ ces_status ensure_device(Basis& b) {
       {M64.data(), M64.size() * 8, (void**)&b.t64.Pm},   {W64.data(), W64.size() * 8, (void**)&b.t64.PwT},
       {M32.data(), M32.size() * 4, (void**)&b.t32.Pm},   {W32.data(), W32.size() * 4, (void**)&b.t32.PwT},
       {cs.data(), cs.size() * 8, (void**)&b.dev_cs},
+      {trig_a.data(), trig_a.size() * 8, (void**)&b.dev_trig_a},
+      {trig_s.data(), trig_s.size() * 8, (void**)&b.dev_trig_s64},
+      {trig_s32.data(), trig_s32.size() * 4, (void**)&b.dev_trig_s32},
       {hart.data(), hart.size() * 8, (void**)&b.dev_hart},
       {b.r.data(), b.r.size() * 8, (void**)&b.dev_rnode},
       {b.wr.data(), b.wr.size() * 8, (void**)&b.dev_wr},
@@ -1326,14 +1367,9 @@ ces_status ces_density(ces_ham hh, int k, const double* d_X, int64_t ldx, const 
     launch_legendre_synth<float>(b, b.t32, G, gbuf, kp, s);
     launch_density_phi<float>(b, gbuf, d_occ, d_rho_grid, k, kp, s);
   }
-  if (d_rho_coef) {   // tau: the forward transform of rho as one 16-column block
-    double* gh = Ptr<double>::at(d_work, ly.gbuf);
-    double* A = Ptr<double>::at(d_work, ly.A);
-    launch_phi_analysis_one(b, d_rho_grid, gh, s);
-    launch_legendre_analysis<double>(b, b.t64, gh, A, kColPad, s);
-    launch_radial_forward<double>(b, b.t64, A, nullptr, 0, nullptr, 0, d_rho_coef, b.d, 1.0, 0.0,
-                                  0.0, false, nullptr, 1, kColPad, s);
-  }
+  if (d_rho_coef)   // tau: the forward transform of rho
+    launch_forward_one(b, d_rho_grid, nullptr, Ptr<double>::at(d_work, ly.gbuf),
+                       Ptr<double>::at(d_work, ly.A), d_rho_coef, s);
   CES_HIP(hipGetLastError());
   return CES_OK;
 }

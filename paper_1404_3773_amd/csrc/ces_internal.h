@@ -55,6 +55,10 @@ struct Basis {
   std::vector<double> legendre;  // [j][l(l+1)/2 + m]
   int device = -1;
   double* dev_cs = nullptr;      // [2][n_phi] cos, sin(2 pi u / n_phi)
+  // MFMA operand tables of the phi transforms (kernels_phi.hip)
+  double* dev_trig_a = nullptr;    // analysis
+  double* dev_trig_s64 = nullptr;  // synthesis, FP64 and FP32
+  float* dev_trig_s32 = nullptr;
   double* dev_rnode = nullptr;   // [n_r] radial nodes
   double* dev_wr = nullptr;      // [n_r] radial weights (r^2 included)
   double* dev_cth = nullptr;     // [n_theta] cos(theta_j)
@@ -186,15 +190,15 @@ void launch_radial_forward(const Basis& b, const DevTables<T>& tb, const T* A, c
                            hipStream_t s);
 
 // Angular stage on MFMA: G -> gbuf (n_r x n_theta x S x kp) -> gh (in place)
-// -> A, as three launches.
+// -> A, as three launches.  n_r: radial nodes of the buffers (0: the basis's).
 template <typename T>
 void launch_legendre_synth(const Basis& b, const DevTables<T>& tb, const T* G, T* gbuf, int kp,
-                           hipStream_t s);
+                           hipStream_t s, int n_r = 0);
 template <typename T>
 void launch_phi_stage(const Basis& b, const T* ab, T* gbuf, int kp, hipStream_t s);
 template <typename T>
 void launch_legendre_analysis(const Basis& b, const DevTables<T>& tb, const T* gbuf, T* A,
-                              int kp, hipStream_t s);
+                              int kp, hipStream_t s, int n_r = 0);
 
 
 // C (k x k, column-major, ld k) = A^T B for d x k blocks, or its symmetric
@@ -236,6 +240,8 @@ template <typename T>
 void launch_kb_apply(const T* P, int64_t d, int64_t ldp, const T* C, T* Z, int n_proj, int k,
                      int kp, hipStream_t s);
 
+// k-steps (of 4) of each half's contraction over m in the phi syntheses
+inline int trig_kt(int L) { return (L + 7) / 8 * 2; }
 // Phi transforms of k grid functions (column i at f + i ldf, [r][j][p]) to /
 // from the Legendre stages' layout g[r][j][s][c] with kp columns (columns k ..
 // kp-1 of the analysis output zeroed).
@@ -248,18 +254,20 @@ void launch_phi_analysis_cols(const Basis& b, const double* f, int64_t ldf, int 
 template <typename T>
 void launch_density_phi(const Basis& b, const T* gbuf, const double* occ, double* rho, int k,
                         int kp, hipStream_t s);
-// gh[r][j][s][c] (16 columns, c > 0 zero) = phi analysis of one grid
-// function f[r][j][p], the input of launch_legendre_analysis with kp = 16.
-void launch_phi_analysis_one(const Basis& b, const double* f, double* gh, hipStream_t s);
-// f[r][j][p] = phi synthesis of column 0 of g (Legendre-synthesis output with
-// kp = 16): one grid function.
-void launch_phi_synthesis_one(const Basis& b, const double* g, double* f, hipStream_t s);
+// One grid function to coefficients z (d values) and back, with the radial
+// nodes as the columns of the angular stages: f [- f2 when given] -> z through
+// gh (n_theta x S x kp) and A (L^2 x kp), kp = n_r rounded up to 16; and f =
+// the inverse transform of x with the radial table RiT through G and g of the
+// same sizes, or with vext the potential vext + f + V_x(rho) [+ v_c(rho) when
+// corr].
+void launch_forward_one(const Basis& b, const double* f, const double* f2, double* gh, double* A,
+                        double* z, hipStream_t s);
+void launch_inverse_one(const Basis& b, const double* RiT, const double* x, double* G, double* g,
+                        double* f, const double* vext, const double* rho, int corr,
+                        hipStream_t s);
 
 // Self-consistent field extras (kernels_scf.hip).
 void launch_sub(const double* a, const double* b, double* out, int64_t n, hipStream_t s);
-// v = vext + v + V_x(rho) [+ v_c(rho) when corr], v holding V_H on entry.
-void launch_ks_finish(const double* vext, const double* rho, double* v, int64_t n, int corr,
-                      hipStream_t s);
 // Perdew-Zunger LDA correlation: vc (and ec when not null) elementwise.
 void launch_pz_correlation(const double* rho, double* vc, double* ec, int64_t n, hipStream_t s);
 // vx = -(3 rho_+ / pi)^(1/3) elementwise (vx may be rho).

@@ -806,246 +806,12 @@ void k_legendre_analysis_fold(const T* __restrict__ PwT,
 }
 
 
-// ------------------------------------------------------------- density
-
-// Density from the Legendre-synthesis output g[r][j][s][i] (Section 2.2.5):
-//   psi_i(r, j, p) = sum_s trig[s][p] g[r][j][s][i],
-//   rho[r][j][p]   = 2 sum_i occ_i psi_i(r, j, p)^2,
-// the phi synthesis of each (r, theta_j) row as a GEMM on MFMA (M = phi
-// points, K = the cos and sin halves of the slots laid out as in the phi
-// stage, N = orbitals in 32-column blocks) with each psi tile squared,
-// weighted and summed over its columns in FP64.  Only the points p <= n_phi/2
-// are formed, their cos part C and sin part S kept apart: since
-// cos(m (n - p)) = cos(m p) and sin(m (n - p)) = -sin(m p), the mirror point
-// has psi(n - p) = C - S next to psi(p) = C + S (p = 0 and p = n/2 are their
-// own mirrors).  Persistent workgroups walk
-// the rows; the (row, column block) g tile goes through LDS with the next one
-// in registers.  The A operand cos / sin(2 pi m p / n_phi) is read from a
-// table of the n_phi angles, its index (m p) mod n_phi advanced by 4p per
-// k-step.  Each wave owns the M tiles wave + 4u and adds their column sums to
-// an LDS row of rho, written out when the row is done.
-constexpr int kDensityWorkgroups = 1024;
-
-template <typename T, int LP>
-__global__ __launch_bounds__(256) void k_density_phi(const T* __restrict__ g,
-                                                     const double* __restrict__ occ,
-                                                     double* __restrict__ rho,
-                                                     const double* __restrict__ cs, AngDims D,
-                                                     int n_phi, int k, int64_t n_rows) {
-  typedef typename MF<T>::acc acc_t;
-  constexpr int GW = 16 * PS_NT + 1;
-  constexpr int K2 = 2 * LP, KPH = LP / 4;
-  constexpr int GPT = K2 / 8;                   // g values per thread per tile
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  const int S = D.S, L = D.L;
-  double* racc = reinterpret_cast<double*>(smem_raw);            // [n_phi]
-  T* ct = reinterpret_cast<T*>(racc + n_phi);                    // [2][n_phi] cos | sin
-  T* gs = ct + 2 * n_phi;                                        // [K2][GW]
-  const int tid = threadIdx.x;
-  const int ii = tid & 31, kr = tid >> 5;
-  const int lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int l16 = lane & 15, kk = lane >> 4;
-  const int ncb = (D.kp + 16 * PS_NT - 1) / (16 * PS_NT);
-  const int phalf = n_phi / 2;                  // points 0..phalf are formed
-  const int nMT = (phalf + 1 + 15) / 16;
-  for (int e = tid; e < 2 * n_phi; e += 256) ct[e] = static_cast<T>(cs[e]);
-  // this thread's g rows (slot s < L -> K row s; slot L + j -> row LP + j)
-  int sof[GPT];
-  bool sok[GPT];
-#pragma unroll
-  for (int u = 0; u < GPT; ++u) {
-    const int kx = kr + 8 * u;
-    const bool sn = kx >= LP;
-    const int kl = sn ? kx - LP : kx;
-    sok[u] = sn ? kl < L - 1 : kl < L;
-    sof[u] = sok[u] ? (sn ? L + kl : kl) * D.kp : 0;
-  }
-  const int64_t rstride = static_cast<int64_t>(S) * D.kp;
-  const int64_t ntask = n_rows * ncb;
-  T gp[GPT];
-  auto fetch = [&](int64_t task) {
-    const int64_t row = task / ncb;
-    const int cb = static_cast<int>(task - row * ncb);
-    const int col = min(cb * 16 * PS_NT + ii, D.kp - 1);
-    const T* gr = g + row * rstride + col;
-#pragma unroll
-    for (int u = 0; u < GPT; ++u) gp[u] = gr[sof[u]];
-  };
-  int64_t task = static_cast<int64_t>(blockIdx.x) * ncb;   // first column block of a row
-  if (task < ntask) fetch(task);
-  for (int64_t row = blockIdx.x; row < n_rows; row += gridDim.x) {
-    for (int e = tid; e < n_phi; e += 256) racc[e] = 0.0;
-    for (int cb = 0; cb < ncb; ++cb) {
-      const int i0 = cb * 16 * PS_NT;
-      const bool ok_col = i0 + ii < D.kp;
-#pragma unroll
-      for (int u = 0; u < GPT; ++u) gs[(kr + 8 * u) * GW + ii] = sok[u] && ok_col ? gp[u] : T(0);
-      __syncthreads();   // gs (and, at cb = 0, the zeroed racc and the tables) visible
-      const int64_t next = cb + 1 < ncb ? row * ncb + cb + 1 : (row + gridDim.x) * ncb;
-      if (next < ntask) fetch(next);                  // next tile, in flight
-      // column weights 2 occ_i of this lane's columns (0 past k)
-      double wcol[PS_NT];
-#pragma unroll
-      for (int nt = 0; nt < PS_NT; ++nt) {
-        const int i = i0 + nt * 16 + l16;
-        wcol[nt] = i < k ? 2.0 * occ[i] : 0.0;
-      }
-      for (int mt = wave; mt < nMT; mt += 4) {
-        const int p = mt * 16 + l16;
-        const int pc = p <= phalf ? p : 0;            // padded rows: any finite value
-        const int d4 = (4 * pc) % n_phi;
-        acc_t acc[2][PS_NT];                          // [cos part, sin part]
-#pragma unroll
-        for (int half = 0; half < 2; ++half)
-#pragma unroll
-          for (int nt = 0; nt < PS_NT; ++nt) acc[half][nt] = zero_acc<acc_t>();
-#pragma unroll
-        for (int half = 0; half < 2; ++half) {
-          // m = 4t + kk (cos half) or 4t + kk + 1 (sin half): u = (m p) mod n_phi
-          int u = ((kk + half) * pc) % n_phi;
-          const T* tb = ct + half * n_phi;
-          const T* grow = gs + (half * LP + kk) * GW + l16;
-#pragma unroll
-          for (int t = 0; t < KPH; ++t) {
-            const T a = tb[u];
-#pragma unroll
-            for (int nt = 0; nt < PS_NT; ++nt)
-              acc[half][nt] = MF<T>::mma(a, grow[4 * t * GW + nt * 16], acc[half][nt]);
-            u += d4;
-            u -= u >= n_phi ? n_phi : 0;
-          }
-        }
-        // psi(p) = C + S and psi(n - p) = C - S: weighted squares summed over
-        // this lane's columns, then over the 16 lanes of a row
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          double sp = 0.0, sm = 0.0;
-#pragma unroll
-          for (int nt = 0; nt < PS_NT; ++nt) {
-            const double c = static_cast<double>(acc[0][nt][v]);
-            const double sn = static_cast<double>(acc[1][nt][v]);
-            const double xp = c + sn, xm = c - sn;
-            sp = fma(wcol[nt] * xp, xp, sp);
-            sm = fma(wcol[nt] * xm, xm, sm);
-          }
-#pragma unroll
-          for (int off = 1; off < 16; off <<= 1) {
-            sp += __shfl_xor(sp, off, 64);
-            sm += __shfl_xor(sm, off, 64);
-          }
-          const int pr = mt * 16 + MF<T>::row(lane, v);
-          if (l16 == 0 && pr <= phalf) {
-            racc[pr] += sp;
-            if (pr > 0 && 2 * pr != n_phi) racc[n_phi - pr] += sm;
-          }
-        }
-      }
-      __syncthreads();   // gs is refilled next; racc complete after the last block
-    }
-    double* out = rho + row * n_phi;
-    for (int e = tid; e < n_phi; e += 256) out[e] = racc[e];
-    __syncthreads();   // racc is zeroed for the next row
-  }
-}
-
-// Column-block phi transforms between grid functions (column i at f + i ldf,
-// [r][theta_j][p]) and the Legendre stages' slot layout g[r][j][s][kp]: the
-// SCF potential and density coefficients (one column, kp = 16) and
-// ces_to_grid / ces_from_grid (k columns).  A workgroup takes four (r, theta_j)
-// rows of one column, one per wave; the angle table cos | sin(2 pi u / n_phi)
-// sits in LDS, and with n_phi <= kOneRowLds also the wave's input row, so the
-// inner loops read LDS only.
-constexpr int kOneRowLds = 1024;
-
-// f_i[r][j][p] = sum_s g[r][j][s][i] trig[s][p]; lane p walks the slots with
-// index (m p) mod n_phi.
-__global__ __launch_bounds__(256) void k_phi_synthesis_cols(const double* __restrict__ g,
-                                                            int kp, double* __restrict__ f,
-                                                            int64_t ldf,
-                                                            const double* __restrict__ cs,
-                                                            int L, int n_phi, int64_t n_rows) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  double* ct = reinterpret_cast<double*>(smem_raw);           // [2][n_phi]
-  double* gw = ct + 2 * n_phi;                                 // [4][S] slot values per wave
-  const int S = 2 * L - 1;
-  const int i = blockIdx.y;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int e = threadIdx.x; e < 2 * n_phi; e += 256) ct[e] = cs[e];
-  const int64_t row = static_cast<int64_t>(blockIdx.x) * 4 + wave;
-  double* gv = gw + wave * S;
-  if (row < n_rows)
-    for (int e = lane; e < S; e += 64) gv[e] = g[(row * S + e) * kp + i];
-  __syncthreads();
-  if (row >= n_rows) return;
-  double* fo = f + static_cast<int64_t>(i) * ldf + row * n_phi;
-  for (int p = lane; p < n_phi; p += 64) {
-    double acc = 0.0;
-    int u = 0;                                   // cos part, m = 0..L-1
-#pragma unroll 4
-    for (int m = 0; m < L; ++m) {
-      acc = fma(gv[m], ct[u], acc);
-      u += p;
-      u -= u >= n_phi ? n_phi : 0;
-    }
-    u = p;                                       // sin part, m = 1..L-1 at slot L - 1 + m
-#pragma unroll 4
-    for (int m = 1; m < L; ++m) {
-      acc = fma(gv[L - 1 + m], ct[n_phi + u], acc);
-      u += p;
-      u -= u >= n_phi ? n_phi : 0;
-    }
-    fo[p] = acc;
-  }
-}
-
-// g[r][j][s][i] = (2 pi / n_phi) sum_p f_i[r][j][p] trig[s][p] for the k
-// columns; the workgroups of the last column also zero columns k .. kp-1.
-// Lane s walks p with index (m p) mod n_phi.
-__global__ __launch_bounds__(256) void k_phi_analysis_cols(const double* __restrict__ f,
-                                                           int64_t ldf, int k, int kp,
-                                                           double* __restrict__ gh,
-                                                           const double* __restrict__ cs,
-                                                           int L, int n_phi, int64_t n_rows) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  double* ct = reinterpret_cast<double*>(smem_raw);           // [2][n_phi]
-  double* fw = ct + 2 * n_phi;                                 // [4][n_phi] when staged
-  const int S = 2 * L - 1;
-  const int i = blockIdx.y;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const bool staged = n_phi <= kOneRowLds;
-  for (int e = threadIdx.x; e < 2 * n_phi; e += 256) ct[e] = cs[e];
-  const int64_t row = static_cast<int64_t>(blockIdx.x) * 4 + wave;
-  const double* fr = f + static_cast<int64_t>(i) * ldf + row * n_phi;
-  if (staged && row < n_rows)
-    for (int e = lane; e < n_phi; e += 64) fw[wave * n_phi + e] = fr[e];
-  __syncthreads();
-  if (row >= n_rows) return;
-  const double* fv = staged ? fw + wave * n_phi : fr;
-  const double dphi = 2.0 * M_PI / n_phi;
-  for (int s = lane; s < S; s += 64) {
-    const int m = s < L ? s : s - L + 1;
-    const double* tb = ct + (s < L ? 0 : n_phi);
-    double acc = 0.0;
-    int u = 0;
-#pragma unroll 4
-    for (int p = 0; p < n_phi; ++p) {
-      acc = fma(fv[p], tb[u], acc);
-      u += m;
-      u -= u >= n_phi ? n_phi : 0;
-    }
-    double* o = gh + (row * S + s) * kp;
-    o[i] = dphi * acc;
-    if (i == k - 1)
-      for (int c = k; c < kp; ++c) o[c] = 0.0;
-  }
-}
-
 }  // namespace
 
 template <typename T>
 void launch_legendre_synth(const Basis& b, const DevTables<T>& tb, const T* G, T* gbuf, int kp,
-                           hipStream_t s) {
+                           hipStream_t s, int n_r) {
+  if (n_r == 0) n_r = b.n_r;
   const AngDims D = ang_dims(b, kp);
   if (b.L > 32) {
     // folded in theta: JT 16-row tiles of the first half of the nodes per wave
@@ -1056,10 +822,10 @@ void launch_legendre_synth(const Basis& b, const DevTables<T>& tb, const T* G, T
     // occupancy they cost (309 atoms, six tiles: 10.3 ms with one against
     // 10.8 with two, at two and five waves per SIMD)
     constexpr int CH = 4;
-    const bool nts = stream_stores<T>(size_t(b.n_r) * b.n_theta * D.S * kp);
+    const bool nts = stream_stores<T>(size_t(n_r) * b.n_theta * D.S * kp);
     auto go = [&](auto nt_tag, int n_ic) {
       constexpr int NT = decltype(nt_tag)::value;
-      dim3 grid(b.n_r * n_ic, (ntile + 3) / 4, D.S);
+      dim3 grid(n_r * n_ic, (ntile + 3) / 4, D.S);
       with_nts(nts, [&](auto nts_tag) {
         constexpr bool NTS = decltype(nts_tag)::value;
         k_legendre_synth_fold<T, NT, 1, CH, NTS><<<grid, 256, 0, s>>>(tb.Pm, G, gbuf, D, n_ic, nh);
@@ -1083,7 +849,7 @@ void launch_legendre_synth(const Basis& b, const DevTables<T>& tb, const T* G, T
   const int ngrp = (b.n_theta + 63) / 64;
   auto go = [&](auto nt_tag, auto jt_tag, int n_ic) {
     constexpr int NT = decltype(nt_tag)::value, JT = decltype(jt_tag)::value;
-    dim3 grid(b.n_r * n_ic, (ngrp + JT - 1) / JT, D.S);
+    dim3 grid(n_r * n_ic, (ngrp + JT - 1) / JT, D.S);
     if constexpr (JT > 1) {
       k_legendre_synth<T, NT, 16, JT><<<grid, 256, 0, s>>>(tb.Pm, G, gbuf, D, n_ic);
     } else {
@@ -1169,11 +935,12 @@ void launch_phi_stage(const Basis& b, const T* ab, T* gbuf, int kp, hipStream_t 
 
 template <typename T>
 void launch_legendre_analysis(const Basis& b, const DevTables<T>& tb, const T* gbuf, T* A,
-                              int kp, hipStream_t s) {
+                              int kp, hipStream_t s, int n_r) {
+  if (n_r == 0) n_r = b.n_r;
   const AngDims D = ang_dims(b, kp);
-  const bool nts = stream_stores<T>(size_t(b.n_r) * D.LL * kp);
+  const bool nts = stream_stores<T>(size_t(n_r) * D.LL * kp);
   const int n_ic = (kp + 16 * LA_NT - 1) / (16 * LA_NT);
-  dim3 grid(b.n_r * n_ic, (D.S + LA_SW - 1) / LA_SW);
+  dim3 grid(n_r * n_ic, (D.S + LA_SW - 1) / LA_SW);
   constexpr bool f32 = sizeof(T) == 4;
   if (b.L > 32) {   // folded in theta; l-tiles of each parity cover ceil(L/2)
     // FP32 on wide blocks: 64 columns per wave share each table fragment
@@ -1183,7 +950,7 @@ void launch_legendre_analysis(const Basis& b, const DevTables<T>& tb, const T* g
     auto go = [&](auto nta_tag) {
       constexpr int NTA = decltype(nta_tag)::value;
       const int n_icf = (kp + 16 * NTA - 1) / (16 * NTA);
-      dim3 gridf(b.n_r * n_icf, (D.S + LA_SW - 1) / LA_SW);
+      dim3 gridf(n_r * n_icf, (D.S + LA_SW - 1) / LA_SW);
       with_nts(nts, [&](auto nts_tag) {
         constexpr bool NTS = decltype(nts_tag)::value;
         if (b.L <= 64)
@@ -1213,65 +980,12 @@ void launch_legendre_analysis(const Basis& b, const DevTables<T>& tb, const T* g
   }
 }
 
-template <typename T>
-void launch_density_phi(const Basis& b, const T* gbuf, const double* occ, double* rho, int k,
-                        int kp, hipStream_t s) {
-  const AngDims D = ang_dims(b, kp);
-  const int64_t n_rows = int64_t(b.n_r) * b.n_theta;
-  dim3 grid(static_cast<unsigned>(std::min<int64_t>(n_rows, kDensityWorkgroups)));
-  const size_t lds = size_t(b.n_phi) * sizeof(double) + 2 * size_t(b.n_phi) * sizeof(T) +
-                     size_t(2 * D.L16) * (16 * PS_NT + 1) * sizeof(T);
-  auto go = [&](auto kern) {
-    // large n_phi needs more than the default 64 KB (set per kernel: the
-    // instantiations share one function-pointer type, so no static flag)
-    if (lds > 65536)
-      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, 163840);
-    kern<<<grid, 256, lds, s>>>(gbuf, occ, rho, b.dev_cs, D, b.n_phi, k, n_rows);
-  };
-  switch (D.L16) {   // L <= 96 (checked at basis creation)
-    case 16: go(&k_density_phi<T, 16>); break;
-    case 32: go(&k_density_phi<T, 32>); break;
-    case 48: go(&k_density_phi<T, 48>); break;
-    case 64: go(&k_density_phi<T, 64>); break;
-    case 80: go(&k_density_phi<T, 80>); break;
-    default: go(&k_density_phi<T, 96>); break;
-  }
-}
-
-void launch_phi_synthesis_cols(const Basis& b, const double* g, int k, int kp, double* f,
-                               int64_t ldf, hipStream_t s) {
-  const int64_t n_rows = int64_t(b.n_r) * b.n_theta;
-  const size_t lds = (2 * size_t(b.n_phi) + 4 * (2 * size_t(b.L) - 1)) * sizeof(double);
-  k_phi_synthesis_cols<<<dim3(static_cast<unsigned>((n_rows + 3) / 4), k), 256, lds, s>>>(
-      g, kp, f, ldf, b.dev_cs, b.L, b.n_phi, n_rows);
-}
-
-void launch_phi_analysis_cols(const Basis& b, const double* f, int64_t ldf, int k, int kp,
-                              double* gh, hipStream_t s) {
-  const int64_t n_rows = int64_t(b.n_r) * b.n_theta;
-  const size_t lds = (2 * size_t(b.n_phi) + (b.n_phi <= kOneRowLds ? 4 * size_t(b.n_phi) : 0)) *
-                     sizeof(double);
-  k_phi_analysis_cols<<<dim3(static_cast<unsigned>((n_rows + 3) / 4), k), 256, lds, s>>>(
-      f, ldf, k, kp, gh, b.dev_cs, b.L, b.n_phi, n_rows);
-}
-
-void launch_phi_synthesis_one(const Basis& b, const double* g, double* f, hipStream_t s) {
-  launch_phi_synthesis_cols(b, g, 1, kColPad, f, b.n_grid, s);
-}
-
-void launch_phi_analysis_one(const Basis& b, const double* f, double* gh, hipStream_t s) {
-  launch_phi_analysis_cols(b, f, b.n_grid, 1, kColPad, gh, s);
-}
-
 #define CES_INST(T)                                                                          \
   template void launch_legendre_synth<T>(const Basis&, const DevTables<T>&, const T*, T*, int, \
-                                         hipStream_t);                                       \
+                                         hipStream_t, int);                                  \
   template void launch_phi_stage<T>(const Basis&, const T*, T*, int, hipStream_t);             \
   template void launch_legendre_analysis<T>(const Basis&, const DevTables<T>&, const T*, T*,   \
-                                            int, hipStream_t);                                 \
-  template void launch_density_phi<T>(const Basis&, const T*, const double*, double*, int, int,  \
-                                      hipStream_t);
+                                            int, hipStream_t, int);
 CES_INST(float)
 CES_INST(double)
 #undef CES_INST

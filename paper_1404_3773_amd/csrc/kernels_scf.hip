@@ -7,6 +7,7 @@
 #include <hip/hip_runtime.h>
 
 #include "ces_internal.h"
+#include "xc.h"
 
 namespace ces {
 
@@ -25,59 +26,11 @@ __global__ void k_sub(const double* __restrict__ a, const double* __restrict__ b
     out[e] = a[e] - b[e];
 }
 
-// Slater (LDA) exchange potential V_x = -(3 rho_+ / pi)^(1/3), rho_+ =
-// max(rho, 0): negative densities from quadrature noise count as zero.
-__device__ __forceinline__ double slater_vx(double rho) {
-  return -cbrt((3.0 / M_PI) * (rho > 0.0 ? rho : 0.0));
-}
-
 // vx[g] = V_x(rho[g]); vx may be rho (each element is read before it is written)
 __global__ void k_slater_x(const double* rho, double* vx, int64_t n) {
   for (int64_t e = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; e < n;
        e += static_cast<int64_t>(gridDim.x) * blockDim.x)
     vx[e] = slater_vx(rho[e]);
-}
-
-// Perdew-Zunger (1981) fit of the Ceperley-Alder correlation energy per
-// electron of the unpolarised gas (the LDA of Section 2.1), r_s =
-// (3 / (4 pi rho))^(1/3):
-//   r_s >= 1:  eps = gamma / (1 + beta1 sqrt(r_s) + beta2 r_s)
-//   r_s < 1:   eps = A ln r_s + B + C r_s ln r_s + D r_s
-// v = d(rho eps)/d rho = eps - (r_s / 3) d eps / d r_s; rho <= 0 gives 0.
-__device__ __forceinline__ void pz81(double rho, double& eps, double& v) {
-  eps = 0.0;
-  v = 0.0;
-  if (!(rho > 0.0)) return;
-  const double rs = cbrt(3.0 / (4.0 * M_PI * rho));
-  if (rs >= 1.0) {
-    const double g = -0.1423, b1 = 1.0529, b2 = 0.3334;
-    const double sq = sqrt(rs), den = 1.0 + b1 * sq + b2 * rs;
-    eps = g / den;
-    // v = eps (1 + 7/6 b1 sqrt(r_s) + 4/3 b2 r_s) / den
-    v = eps * (1.0 + (7.0 / 6.0) * b1 * sq + (4.0 / 3.0) * b2 * rs) / den;
-  } else {
-    const double A = 0.0311, B = -0.048, C = 0.0020, D = -0.0116;
-    const double ln = log(rs);
-    eps = A * ln + B + C * rs * ln + D * rs;
-    v = A * ln + (B - A / 3.0) + (2.0 / 3.0) * C * rs * ln + ((2.0 * D - C) / 3.0) * rs;
-  }
-}
-
-// v[g] = vext[g] + v[g] + V_x(rho[g]) [+ v_c(rho[g]) when corr]   (v holds
-// V_H on entry)
-__global__ void k_ks_finish(const double* __restrict__ vext, const double* __restrict__ rho,
-                            double* __restrict__ v, int64_t n, int corr) {
-  for (int64_t e = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; e < n;
-       e += static_cast<int64_t>(gridDim.x) * blockDim.x) {
-    const double r = rho[e];
-    double out = vext[e] + v[e] + slater_vx(r);
-    if (corr) {
-      double eps, vc;
-      pz81(r, eps, vc);
-      out += vc;
-    }
-    v[e] = out;
-  }
 }
 
 // vc[g] = v_c(rho[g]) and, when ec is not null, ec[g] = eps_c(rho[g]); vc may
@@ -151,11 +104,6 @@ __global__ __launch_bounds__(256) void k_sad_density(
 
 void launch_sub(const double* a, const double* b, double* out, int64_t n, hipStream_t s) {
   k_sub<<<grid1d(n), 256, 0, s>>>(a, b, out, n);
-}
-
-void launch_ks_finish(const double* vext, const double* rho, double* v, int64_t n, int corr,
-                      hipStream_t s) {
-  k_ks_finish<<<grid1d(n), 256, 0, s>>>(vext, rho, v, n, corr);
 }
 
 void launch_pz_correlation(const double* rho, double* vc, double* ec, int64_t n,

@@ -21,19 +21,6 @@ namespace {
 constexpr int kLanczosSteps = 20;
 constexpr int kMaxHistory = 64;
 
-// Inverse transform of one coefficient vector with the Hartree radial table
-// in place of R_ln: V_H on the grid.
-void hartree_to_grid(const Basis& b, const Layout& ly, void* work, const double* tau,
-                     double* vh, hipStream_t s) {
-  DevTables<double> th = b.t64;
-  th.RiT = b.dev_hart;
-  double* G = Ptr<double>::at(work, ly.G);
-  double* g = Ptr<double>::at(work, ly.gbuf);
-  launch_radial_inverse<double>(b, th, tau, b.d, G, 1, kColPad, s);
-  launch_legendre_synth<double>(b, b.t64, G, g, kColPad, s);
-  launch_phi_synthesis_one(b, g, vh, s);
-}
-
 // min || sum_t c_t F_t ||_2 subject to sum_t c_t = 1 over the columns in
 // `cols`, from their Gram matrix G (m x m, column-major over all columns):
 // the bordered system [G 1; 1^T 0] [c; mu] = [0; 1], solved by Gaussian
@@ -298,7 +285,10 @@ ces_status ces_hartree(ces_ham hh, const double* d_tau, double* d_vh, void* d_wo
   if (!d_tau || !d_vh) return fail(CES_ERR_INVALID_ARG, "null coefficients or output");
   Layout ly;
   CES_TRY(check_work(h, 1, CES_PREC_FP64, d_work, work_bytes, ly));
-  hartree_to_grid(*h.basis, ly, d_work, d_tau, d_vh, static_cast<hipStream_t>(stream));
+  // the inverse transform with the Hartree radial table in place of R_ln
+  launch_inverse_one(*h.basis, h.basis->dev_hart, d_tau, Ptr<double>::at(d_work, ly.G),
+                     Ptr<double>::at(d_work, ly.gbuf), d_vh, nullptr, nullptr, 0,
+                     static_cast<hipStream_t>(stream));
   CES_HIP(hipGetLastError());
   return CES_OK;
 }
@@ -319,15 +309,11 @@ ces_status ces_ks_potential(ces_ham hh, const double* d_rho, const double* d_rho
   // larger density basis on the same grid (Section 2.2.5)
   const Basis& b = h.rho_basis ? *h.rho_basis : *h.basis;
   double* tau = d_tau ? d_tau : Ptr<double>::at(d_work, ly.V3);
-  double* A = Ptr<double>::at(d_work, ly.A);
   double* gh = Ptr<double>::at(d_work, ly.gbuf);
-  launch_sub(d_rho, d_rho_ion, d_v, b.n_grid, s);                  // d_v <- rho - rho_ion
-  launch_phi_analysis_one(b, d_v, gh, s);                          // forward transform
-  launch_legendre_analysis<double>(b, b.t64, gh, A, kColPad, s);
-  launch_radial_forward<double>(b, b.t64, A, nullptr, 0, nullptr, 0, tau, b.d, 1.0, 0.0, 0.0,
-                                false, nullptr, 1, kColPad, s);
-  hartree_to_grid(b, ly, d_work, tau, d_v, s);                      // d_v <- V_H
-  launch_ks_finish(d_vext, d_rho, d_v, b.n_grid, h.xc_correlation, s);   // + V_ext + V_xc
+  // coefficients of rho - rho_ion, then V_H on the grid with V_ext and V_xc
+  launch_forward_one(b, d_rho, d_rho_ion, gh, Ptr<double>::at(d_work, ly.A), tau, s);
+  launch_inverse_one(b, b.dev_hart, tau, Ptr<double>::at(d_work, ly.G), gh, d_v, d_vext, d_rho,
+                     h.xc_correlation, s);
   CES_HIP(hipGetLastError());
   return CES_OK;
 }
