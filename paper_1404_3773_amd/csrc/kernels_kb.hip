@@ -514,19 +514,284 @@ void k_kb_apply_wide(const T* __restrict__ P, int64_t d, int64_t ldp, const T* _
       }
 }
 
-// C[q][i] = h_q sum_c part[c][q][i] for i < k (chunks in order), 0 for k <= i < kp.
+// ------------------------------------------- FP32 products on bf16 MFMA
+//
+// An FP32 value is the exact sum of three bf16 values, x = h + m + l (each the
+// rounding of what the former leave: 8 significant bits each, 24 in all), so
+// x y = hh' + (hm' + mh') + (hl' + mm' + lh') up to the dropped ml', lm' and
+// ll' terms, which stay below 2^-24 |x y|: one FP32 rounding of the product.
+// The six products run on bf16 MFMA with FP32 accumulators.  A 16x16x32 bf16
+// MFMA takes as long as half a 16x16x4 FP32 one (2,416 against 144 TFLOP/s in
+// register-only loops), so the six cost 0.37 of the FP32 MFMAs, and a K = 32
+// step rounds each accumulator 6 times instead of 8.  Against 64 bits the
+// results are no further off than the FP32 kernels' (H X of the 309-atom shape
+// below, relative 2-norm: 6.6e-8 against 9.1e-8).  The split keeps FP32's exponent range; values above the
+// largest bf16 (3.39e38) round to infinity, and an infinite or NaN input
+// makes the outputs of its row or column NaN.
+//
+// Workgroup: 256 x 256 outputs, 8 waves of 64 x 128 (128 accumulators per
+// lane, two waves per SIMD), K in steps of 32 staged in one LDS buffer (98
+// KB) as bf16 planes [operand][plane][row][32 k]; a row's four 16-byte pieces
+// are rotated by its number so that the operand reads (16 rows of one piece)
+// and the staging writes fall on distinct banks.  The next step's values are
+// loaded into registers while the current one runs, and split on the way to
+// LDS: 5.5 vector instructions per value, used for 256 outputs.
+// 309 atoms (1236 projectors, k = 500), FP32 kernels -> split: C = P^T Y 11.0
+// -> 5.9 ms, Z = P C 9.9 -> 6.2 ms; bf16 MFMA busy 0.60 of the time at about
+// 2.1 GHz, the rest is the staging between the two barriers of a step.  Tiles
+// of 128 x 256 double-buffered in 147 KB: 6.4 and 7.9 ms (half as much reuse
+// of each staged value); leaving out the MFMA tiles past a narrow block by
+// branches in this kernel: 219 registers spilled.
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f2 __attribute__((ext_vector_type(2)));
+constexpr int kSplitM = 256, kSplitN = 256, kSplitK = 32;
+constexpr size_t kSplitLds = size_t(3) * (kSplitM + kSplitN) * kSplitK * 2;
+
+__device__ __forceinline__ unsigned pack_bf16(float a, float b) {
+  const f2 x = {a, b};
+  return __builtin_bit_cast(unsigned, __builtin_convertvector(x, bf16x2));
+}
+// The bf16 parts of two values, packed in pairs.
+__device__ __forceinline__ void split_pair(float a, float b, unsigned (&p)[3]) {
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    p[i] = pack_bf16(a, b);
+    a -= __builtin_bit_cast(float, p[i] << 16);
+    b -= __builtin_bit_cast(float, p[i] & 0xffff0000u);
+  }
+}
+
+// D[m][n] = sum_k A(m, k) B(n, k) for one 256 x 256 tile and k in [k0, k1).
+// KM: both operands run along k (element (row, k) at row ld + k, 16-byte
+// aligned rows whose length is a multiple of 4); else along the rows (element
+// at k ld + row).  Rows past nA / nB repeat the last one (their outputs are
+// not stored); k past k1 counts as zero (only the last step can hold such
+// k).  Addresses are a scalar base and one 32-bit lane offset per load (forming
+// 64-bit lane addresses took as many vector instructions as the split:
+// Z = P C 6.8 -> 6.2 ms).
+template <bool KM>
+__device__ __forceinline__ void split_tile(const float* __restrict__ A, int64_t lda, int64_t a0,
+                                           int64_t nA, const float* __restrict__ B, int64_t ldb,
+                                           int64_t b0, int64_t nB, int64_t k0, int64_t k1,
+                                           uint4* lds, f4 (&acc)[4][8]) {
+  constexpr int R = 256;
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, kk = lane >> 4;
+  const int mA = static_cast<int>(min(nA - a0, int64_t(R)));   // rows of this tile
+  const int mB = static_cast<int>(min(nB - b0, int64_t(R)));
+  // 16-byte piece c of (operand o, plane p, row r)
+  auto at = [](int o, int p, int r, int c) {
+    return ((o * 3 + p) * R + r) * 4 + (c ^ ((r >> 1) & 3));
+  };
+  // KM: 8 threads per row, 64 rows per pass q; else one row and 16 k per
+  // thread, of either operand
+  constexpr int NP = KM ? 4 : 1;
+  const float* base[2][NP];
+  unsigned off[2][NP];
+#pragma unroll
+  for (int o = 0; o < 2; ++o)
+#pragma unroll
+    for (int q = 0; q < NP; ++q) {
+      const int m = o ? mB : mA;
+      const int g = KM ? 64 * q : 64 * (wave & 3);
+      const int r = g + (KM ? tid >> 3 : lane);
+      const int g0 = KM ? min(g, m - 1) : 0, rc = min(r, m - 1);
+      const int64_t ld = o ? ldb : lda;
+      base[o][q] = (o ? B : A) + (o ? b0 + g0 : a0 + g0) * (KM ? ld : 1);
+      off[o][q] = KM ? static_cast<unsigned>((rc - g0) * ld) + 4 * (tid & 7) : unsigned(rc);
+    }
+  const int kw = KM ? 0 : 16 * (wave >> 2);
+  float v[2][16];
+  auto fetch = [&](int64_t kb) __attribute__((always_inline)) {
+    // KM: a vector past the last aligned one of the chunk reads that one
+    const int64_t rest = (k1 - 1 - kb) / 4 * 4;
+    const int back = KM && 4 * (tid & 7) > rest ? static_cast<int>(4 * (tid & 7) - rest) : 0;
+#pragma unroll
+    for (int o = 0; o < 2; ++o) {
+      if constexpr (KM) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          float x[4];
+          load_vec<float, 4>(base[o][q] + kb + (off[o][q] - back), x);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[o][4 * q + e] = x[e];
+        }
+      } else {
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+          const int64_t k = kb + kw + j;
+          v[o][j] = (base[o][0] + (k < k1 ? k : k1 - 1) * (o ? ldb : lda))[off[o][0]];
+        }
+      }
+    }
+  };
+  auto stage = [&](int64_t kb) __attribute__((always_inline)) {
+    if (kb + kSplitK > k1) {          // the last step of a chunk: k past k1
+#pragma unroll
+      for (int o = 0; o < 2; ++o)
+#pragma unroll
+        for (int j = 0; j < 16; ++j)
+          if (kb + (KM ? 4 * (tid & 7) + j % 4 : kw + j) >= k1) v[o][j] = 0.0f;
+    }
+#pragma unroll
+    for (int o = 0; o < 2; ++o) {
+      if constexpr (KM) {
+        uint2* l2 = reinterpret_cast<uint2*>(lds);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          unsigned p0[3], p1[3];
+          split_pair(v[o][4 * q], v[o][4 * q + 1], p0);
+          split_pair(v[o][4 * q + 2], v[o][4 * q + 3], p1);
+#pragma unroll
+          for (int p = 0; p < 3; ++p)
+            l2[2 * at(o, p, (tid >> 3) + 64 * q, (tid & 7) >> 1) + (tid & 1)] =
+                make_uint2(p0[p], p1[p]);
+        }
+      } else {
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {     // 16-byte pieces
+          unsigned w[4][3];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) split_pair(v[o][8 * g + 2 * e], v[o][8 * g + 2 * e + 1], w[e]);
+#pragma unroll
+          for (int p = 0; p < 3; ++p)
+            lds[at(o, p, tid & 255, kw / 8 + g)] = make_uint4(w[0][p], w[1][p], w[2][p], w[3][p]);
+        }
+      }
+    }
+  };
+  const int ra = (wave >> 1) * 64 + l16, rb = (wave & 1) * 128 + l16;
+  auto compute = [&]() __attribute__((always_inline)) {
+    bf16x8 a[4][3];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int p = 0; p < 3; ++p)
+        a[u][p] = __builtin_bit_cast(bf16x8, lds[at(0, p, ra + 16 * u, kk)]);
+#pragma unroll
+    for (int w = 0; w < 8; ++w) {
+      bf16x8 b[3];
+#pragma unroll
+      for (int p = 0; p < 3; ++p)
+        b[p] = __builtin_bit_cast(bf16x8, lds[at(1, p, rb + 16 * w, kk)]);
+      // smallest terms first
+#pragma unroll
+      for (int t = 0; t < 6; ++t) {
+        constexpr int PA[6] = {2, 1, 0, 1, 0, 0}, PB[6] = {0, 1, 2, 0, 1, 0};
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          acc[u][w] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[u][PA[t]], b[PB[t]], acc[u][w], 0,
+                                                              0, 0);
+      }
+    }
+  };
+  fetch(k0);
+  for (int64_t kb = k0; kb < k1; kb += kSplitK) {
+    stage(kb);
+    __syncthreads();
+    if (kb + kSplitK < k1) fetch(kb + kSplitK);     // next step's values, in flight
+    compute();
+    __syncthreads();
+  }
+}
+
+// C = P^T Y: one split-K chunk's partial product; workgroups of a chunk share
+// an XCD (chunk mod 8), so its L2 serves the rows they have in common.
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void k_kb_gemm_split(const float* __restrict__ P, int64_t d, int64_t ldp,
+                     const float* __restrict__ Y, int64_t ldy, float* __restrict__ part,
+                     int n_proj, int k, int kp, int64_t kchunk, int nM, int nN, int nchunk) {
+  extern __shared__ __align__(16) unsigned char kb_smem[];
+  const int x = blockIdx.x & 7, j = blockIdx.x >> 3;
+  const int per = nM * nN;
+  const int chunk = x + 8 * (j / per);
+  if (chunk >= nchunk) return;
+  const int tile = j % per, mt = tile / nN, nt = tile - mt * nN;
+  const int64_t k0 = static_cast<int64_t>(chunk) * kchunk;
+  const int64_t k1 = k0 + kchunk < d ? k0 + kchunk : d;
+  f4 acc[4][8];
+#pragma unroll
+  for (int u = 0; u < 4; ++u)
+#pragma unroll
+    for (int w = 0; w < 8; ++w) acc[u][w] = zero_acc<f4>();
+  split_tile<true>(P, ldp, int64_t(mt) * kSplitM, n_proj, Y, ldy, int64_t(nt) * kSplitN, k,
+                   k0, k1, reinterpret_cast<uint4*>(kb_smem), acc);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  float* pc = part + static_cast<int64_t>(chunk) * n_proj * kp;
+#pragma unroll
+  for (int u = 0; u < 4; ++u)
+#pragma unroll
+    for (int w = 0; w < 8; ++w)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int q = mt * kSplitM + (wave >> 1) * 64 + 16 * u + MF<float>::row(lane, r);
+        const int i = nt * kSplitN + (wave & 1) * 128 + 16 * w + (lane & 15);
+        if (q < n_proj && i < k) pc[static_cast<int64_t>(q) * kp + i] = acc[u][w][r];
+      }
+}
+
+// Z = P C: tile 256 columns i x 256 rows alpha; the workgroups of one alpha
+// tile share an XCD.
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void k_kb_apply_split(const float* __restrict__ P, int64_t d, int64_t ldp,
+                      const float* __restrict__ C, int n_proj, int k, int kp,
+                      float* __restrict__ Z, int nI, int nA) {
+  extern __shared__ __align__(16) unsigned char kb_smem[];
+  const int x = blockIdx.x & 7, j = blockIdx.x >> 3;
+  const int ga = x + 8 * (j / nI), it = j - (j / nI) * nI;
+  if (ga >= nA) return;
+  f4 acc[4][8];
+#pragma unroll
+  for (int u = 0; u < 4; ++u)
+#pragma unroll
+    for (int w = 0; w < 8; ++w) acc[u][w] = zero_acc<f4>();
+  split_tile<false>(C, kp, int64_t(it) * kSplitM, k, P, ldp, int64_t(ga) * kSplitN, d, 0,
+                    n_proj, reinterpret_cast<uint4*>(kb_smem), acc);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int u = 0; u < 4; ++u)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int i = it * kSplitM + (wave >> 1) * 64 + 16 * u + MF<float>::row(lane, r);
+      if (i >= k) continue;
+#pragma unroll
+      for (int w = 0; w < 8; ++w) {
+        const int64_t a = static_cast<int64_t>(ga) * kSplitN + (wave & 1) * 128 + 16 * w +
+                          (lane & 15);
+        if (a < d) Z[static_cast<int64_t>(i) * d + a] = acc[u][w][r];
+      }
+    }
+}
+
+// C[q][i] = h_q sum_c part[c][q][i] for i < k, 0 for k <= i < kp.  A workgroup
+// takes 32 elements; 8 threads share an element's chunks (c mod 8) and their
+// sums are added in order, so up to 512 chunks take 64 loads in a row instead
+// of 512 (13 x 16 elements, 512 chunks: 140 us in one thread each).
 template <typename T>
-__global__ void k_kb_reduce(const T* __restrict__ part, int nchunk, const T* __restrict__ h,
-                            T* __restrict__ C, int n_proj, int k, int kp) {
+__global__ __launch_bounds__(256) void k_kb_reduce(const T* __restrict__ part, int nchunk,
+                                                   const T* __restrict__ h, T* __restrict__ C,
+                                                   int n_proj, int k, int kp) {
+  __shared__ T sum[8][32];
   const int64_t n = static_cast<int64_t>(n_proj) * kp;
-  const int64_t stride = n;
-  for (int64_t e = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; e < n;
-       e += static_cast<int64_t>(gridDim.x) * blockDim.x) {
+  const int el = threadIdx.x & 31, g = threadIdx.x >> 5;
+  for (int64_t e0 = blockIdx.x * int64_t(32); e0 < n; e0 += gridDim.x * int64_t(32)) {
+    const int64_t e = e0 + el;
     const int q = static_cast<int>(e / kp), i = static_cast<int>(e - static_cast<int64_t>(q) * kp);
     T s = T(0);
-    if (i < k)
-      for (int c = 0; c < nchunk; ++c) s += part[c * stride + e];
-    C[e] = h[q] * s;
+    if (e < n && i < k)
+#pragma unroll 4
+      for (int c = g; c < nchunk; c += 8) s += part[c * n + e];
+    sum[g][el] = s;
+    __syncthreads();
+    if (g == 0 && e < n) {
+#pragma unroll
+      for (int j = 1; j < 8; ++j) s += sum[j][el];
+      C[e] = h[q] * s;
+    }
+    __syncthreads();
   }
 }
 
@@ -543,26 +808,29 @@ inline unsigned kb_workgroups(int nchunk, int nM, int nN, bool xcd_chunk) {
   return static_cast<unsigned>(8 * per_xcd * nN);
 }
 
-template <typename S>
-KbGrid kb_grid(int n_proj, int k, int64_t d) {
-  constexpr int KB = S::KB;
+// Split-K grid of tiles BM x BN and KB alpha per step with 8 c chunks, c per
+// XCD: the c that minimises rounds x (steps per chunk + 4), with rounds of
+// `slots` resident workgroups per XCD and about 4 steps' time to start and
+// end a chunk, plus the partial sums' traffic (an element written and read
+// costs about 1 / 1.5 M of a step).  Few tiles (small blocks or few
+// projectors) take many short chunks, so that every CU has work: 13
+// projectors x 4 columns, d = 162,000: 32 chunks of 158 steps left 7/8 of the
+// chip idle.
+KbGrid kb_grid_for(int BM, int BN, int KB, int slots, int n_proj, int k, int64_t d) {
   KbGrid gr;
-  gr.nM = (n_proj + 32 * S::TM - 1) / (32 * S::TM);
-  gr.nN = (k + 32 * S::TN - 1) / (32 * S::TN);
-  // 8 c chunks (c per XCD, each XCD's workgroups c nM nN), c <= 4 chosen so
-  // that those workgroups fill whole rounds of kKbPerXcd resident ones as
-  // nearly as possible (309 atoms, FP32: nM = 10, nN = 8, c = 4: 5 full
-  // rounds); chunks of at least 16 steps
+  gr.nM = (n_proj + BM - 1) / BM;
+  gr.nN = (k + BN - 1) / BN;
   const int64_t steps = (d + KB - 1) / KB;
+  const double elems = double(n_proj) * gr.nN * BN;
   int c_best = 1;
-  double waste_best = 2.0;
-  for (int c = 1; c <= 4; ++c) {
-    if (c > 1 && steps < int64_t(8 * c) * 16) break;
-    const int64_t wg = int64_t(c) * gr.nM * gr.nN;
-    const int64_t rounds = (wg + kKbPerXcd - 1) / kKbPerXcd;
-    const double waste = double(rounds * kKbPerXcd - wg) / double(rounds * kKbPerXcd);
-    if (waste < waste_best - 1e-9) {
-      waste_best = waste;
+  double best = 1e300;
+  for (int c = 1; c <= 64; ++c) {
+    const int64_t per = (steps + 8 * c - 1) / (8 * c);   // steps per chunk
+    if (c > 1 && per < 4) break;
+    const int64_t rounds = (int64_t(c) * gr.nM * gr.nN + slots - 1) / slots;
+    const double cost = double(rounds) * double(per + 4) + 8.0 * c * elems / 1.5e6;
+    if (cost < best) {
+      best = cost;
       c_best = c;
     }
   }
@@ -571,6 +839,20 @@ KbGrid kb_grid(int n_proj, int k, int64_t d) {
   gr.nchunk = static_cast<int>((d + gr.kchunk - 1) / gr.kchunk);
   return gr;
 }
+template <typename S>
+KbGrid kb_grid(int n_proj, int k, int64_t d) {
+  return kb_grid_for(32 * S::TM, 32 * S::TN, S::KB, kKbPerXcd, n_proj, k, d);
+}
+KbGrid kb_split_grid(int n_proj, int k, int64_t d) {
+  return kb_grid_for(kSplitM, kSplitN, kSplitK, 32, n_proj, k, d);   // one workgroup per CU
+}
+
+// FP32 products with at least 96 projectors and more than 128 columns run on
+// the split kernels.  Below, their 256 x 256 tiles are mostly padding (d =
+// 162,000, C and Z = P C in us, FP32 | split: 192 projectors, k = 128: 168, 97
+// | 166, 110; k = 200: 218, 150 | 168, 116; 64 projectors, k = 200: 160, 70 |
+// 158, 54; 512, k = 512: 716, 706 | 411, 467).
+inline bool kb_split(int n_proj, int k) { return n_proj >= 96 && k > 128; }
 
 }  // namespace
 
@@ -580,13 +862,17 @@ KbGrid kb_grid(int n_proj, int k, int64_t d) {
 size_t kb_partial_bytes(int n_proj, int k, int64_t d) {
   if (n_proj <= 0) return 0;
   size_t most = 0;
-  for (int kc = 1; kc <= k; ++kc) {
+  // the grids depend on kc through ceil(kc / 64) at most
+  for (int kc = std::min(k, 64);; kc = std::min(kc + 64, k)) {
     const size_t kp = size_t(round_up(kc, kColPad));
-    const size_t c32 = size_t(std::max(kb_grid<KgVec>(n_proj, kc, d).nchunk,
-                                       kb_grid<KbShape<float>>(n_proj, kc, d).nchunk)) *
+    const size_t c32 = size_t(std::max({kb_grid<KgVec>(n_proj, kc, d).nchunk,
+                                        kb_grid<KbShape<float>>(n_proj, kc, d).nchunk,
+                                        kb_split(n_proj, kc) ? kb_split_grid(n_proj, kc, d).nchunk
+                                                             : 0})) *
                        sizeof(float);
     const size_t c64 = size_t(kb_grid<KbShape<double>>(n_proj, kc, d).nchunk) * sizeof(double);
     most = std::max(most, std::max(c32, c64) * size_t(n_proj) * kp);
+    if (kc == k) break;
   }
   return most;
 }
@@ -633,7 +919,14 @@ void launch_kb_gemm(const T* P, int64_t d, int64_t ldp, const T* Y, int64_t ldy,
     nchunk = gr.nchunk;
   };
   if constexpr (sizeof(T) == 4) {
-    if (ldp % 4 == 0 && ldy % 4 == 0 && reinterpret_cast<uintptr_t>(P) % 16 == 0 &&
+    if (kb_split(n_proj, k) && ldp % 4 == 0 && ldy % 4 == 0 &&
+        reinterpret_cast<uintptr_t>(P) % 16 == 0 && reinterpret_cast<uintptr_t>(Y) % 16 == 0) {
+      const KbGrid gr = kb_split_grid(n_proj, k, d);
+      allow_lds(&k_kb_gemm_split, kSplitLds);
+      k_kb_gemm_split<<<8 * ((gr.nchunk + 7) / 8) * gr.nM * gr.nN, 512, kSplitLds, s>>>(
+          P, d, ldp, Y, ldy, part, n_proj, k, kp, gr.kchunk, gr.nM, gr.nN, gr.nchunk);
+      nchunk = gr.nchunk;
+    } else if (ldp % 4 == 0 && ldy % 4 == 0 && reinterpret_cast<uintptr_t>(P) % 16 == 0 &&
         reinterpret_cast<uintptr_t>(Y) % 16 == 0)
       go(KgVec{}, std::false_type{}, std::integral_constant<int, 4>{});
     else
@@ -646,7 +939,7 @@ void launch_kb_gemm(const T* P, int64_t d, int64_t ldp, const T* Y, int64_t ldy,
       go(KbShape<double>{}, std::false_type{}, std::integral_constant<int, 1>{});
   }
   const int64_t n = int64_t(n_proj) * kp;
-  const unsigned rb = static_cast<unsigned>(std::min<int64_t>((n + 255) / 256, 4096));
+  const unsigned rb = static_cast<unsigned>(std::min<int64_t>((n + 31) / 32, 8192));
   k_kb_reduce<T><<<rb, 256, 0, s>>>(part, nchunk, h, C, n_proj, k, kp);
 }
 
@@ -680,6 +973,16 @@ int launch_atb_partial(const double* A, int64_t lda, const double* B, int64_t ld
 template <typename T>
 void launch_kb_apply(const T* P, int64_t d, int64_t ldp, const T* C, T* Z, int n_proj, int k,
                      int kp, hipStream_t s) {
+  if constexpr (sizeof(T) == 4) {
+    if (kb_split(n_proj, k)) {
+      const int nI = (k + kSplitM - 1) / kSplitM;
+      const int nA = static_cast<int>((d + kSplitN - 1) / kSplitN);
+      allow_lds(&k_kb_apply_split, kSplitLds);
+      k_kb_apply_split<<<8 * ((nA + 7) / 8) * nI, 512, kSplitLds, s>>>(P, d, ldp, C, n_proj, k, kp,
+                                                                       Z, nI, nA);
+      return;
+    }
+  }
   // wide tiles when the 16-byte column loads stay aligned
   constexpr int VW = 16 / static_cast<int>(sizeof(T));
   if (ldp % VW == 0 && kp % VW == 0 && reinterpret_cast<uintptr_t>(P) % 16 == 0 &&
