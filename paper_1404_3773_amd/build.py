@@ -16,7 +16,7 @@ LIB = os.path.join(HERE, "libces.so")
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 
 SOURCES = ["kernels.hip", "kernels_angular.hip", "kernels_radial.hip", "kernels_scf.hip",
-           "kernels_phi.hip", "kernels_mlp.hip", "kernels_block.hip", "kernels_kb.hip", "kernels_lobpcg.hip", "noalloc.hip", "capi.cpp", "lobpcg.cpp", "scf.cpp", "learned.cpp", "setup_tables.cpp"]
+           "kernels_phi.hip", "kernels_fused.hip", "kernels_mlp.hip", "kernels_block.hip", "kernels_kb.hip", "kernels_lobpcg.hip", "noalloc.hip", "capi.cpp", "lobpcg.cpp", "scf.cpp", "learned.cpp", "setup_tables.cpp"]
 
 # Device code: gfx950 only; packed-FP32 instructions disabled.  MFMA results
 # stay in VGPRs: by itself the compiler puts them in AGPRs and copies them out

@@ -244,6 +244,16 @@ ces_status ensure_device(Basis& b) {
             4.0 * M_PI / (2 * l + 1) * c0 * b.R * std::pow(b.r[kk] / b.R, l) / k;
       }
     }
+  // fused angular stage (FP32 tables rounded from their FP64 values)
+  std::vector<double> ft, fa, fc, ft32, fa32, fc32, dir, dir32;
+  std::vector<float> gt, ga, gc;
+  if (b.L <= kFusedL) {
+    fused_tables(b, false, ft, fa, fc, dir);
+    fused_tables(b, true, ft32, fa32, fc32, dir32);
+    gt.assign(ft32.begin(), ft32.end());
+    ga.assign(fa32.begin(), fa32.end());
+    gc.assign(fc32.begin(), fc32.end());
+  }
   std::vector<int> lay(2 * size_t(b.L));
   std::vector<double> lam(b.d);
   for (int l = 0; l < b.L; ++l) {
@@ -276,6 +286,10 @@ ces_status ensure_device(Basis& b) {
       {trig_a.data(), trig_a.size() * 8, (void**)&b.dev_trig_a},
       {trig_s.data(), trig_s.size() * 8, (void**)&b.dev_trig_s64},
       {trig_s32.data(), trig_s32.size() * 4, (void**)&b.dev_trig_s32},
+      {ft.data(), ft.size() * 8, (void**)&b.f64.T12}, {fa.data(), fa.size() * 8, (void**)&b.f64.PA},
+      {fc.data(), fc.size() * 8, (void**)&b.f64.PC},  {gt.data(), gt.size() * 4, (void**)&b.f32.T12},
+      {ga.data(), ga.size() * 4, (void**)&b.f32.PA},  {gc.data(), gc.size() * 4, (void**)&b.f32.PC},
+      {dir.data(), dir.size() * 8, (void**)&b.dev_dir},
       {hart.data(), hart.size() * 8, (void**)&b.dev_hart},
       {b.r.data(), b.r.size() * 8, (void**)&b.dev_rnode},
       {b.wr.data(), b.wr.size() * 8, (void**)&b.dev_wr},
@@ -290,7 +304,8 @@ ces_status ensure_device(Basis& b) {
   size_t off = 0;
   for (auto& p : pieces) {
     *p.dst = static_cast<char*>(blk) + off;
-    if (hipMemcpy(*p.dst, p.src, p.bytes, hipMemcpyHostToDevice) != hipSuccess) {
+    if (p.bytes > 0 &&
+        hipMemcpy(*p.dst, p.src, p.bytes, hipMemcpyHostToDevice) != hipSuccess) {
       (void)hipFree(blk);
       return fail(CES_ERR_DEVICE, "upload of basis tables failed");
     }
@@ -447,6 +462,13 @@ template <>
 const DevTables<float>& tables<float>(const Basis& b) { return b.t32; }
 
 template <typename T>
+const FusedTables<T>& fused_of(const Basis& b);
+template <>
+const FusedTables<double>& fused_of<double>(const Basis& b) { return b.f64; }
+template <>
+const FusedTables<float>& fused_of<float>(const Basis& b) { return b.f32; }
+
+template <typename T>
 const T* ab_of(const Ham& h);
 template <>
 const double* ab_of<double>(const Ham& h) { return h.ab64; }
@@ -483,26 +505,34 @@ ces_status h_step_block(Ham& h, const Layout& ly, void* work, int k, const T* Yi
     launch_kb_apply<T>(Pd, b.d, ldp, C, Zkb, h.n_proj, k, kp, s);
   }
   T* gbuf = Ptr<T>::at(work, ly.gbuf);
+  T* A2 = nullptr;
   {
     StageTimer t(stage_id<T>(ST_RADIAL_INV), s);
     launch_radial_inverse<T>(b, tb, Yin, ldin, G, k, kp, s);
   }
-  {
-    StageTimer t(stage_id<T>(ST_LEG_SYNTH), s);
-    launch_legendre_synth<T>(b, tb, G, gbuf, kp, s);
-  }
-  {
+  if (b.L <= kFusedL) {
+    // one kernel from G to A (timed as the phi stage); a second part of A
+    // takes the place of g
     StageTimer t(stage_id<T>(ST_PHI), s);
-    launch_phi_stage<T>(b, ab_of<T>(h), gbuf, kp, s);
-  }
-  {
+    const int parts = fused_parts(b, kp, size_t(b.n_r) * b.n_theta * (2 * size_t(b.L) - 1) * kp);
+    if (parts == 2) A2 = gbuf;
+    launch_angular_fused<T>(b, fused_of<T>(b), ab_of<T>(h), G, A, gbuf, parts, kp, s);
+  } else {
+    {
+      StageTimer t(stage_id<T>(ST_LEG_SYNTH), s);
+      launch_legendre_synth<T>(b, tb, G, gbuf, kp, s);
+    }
+    {
+      StageTimer t(stage_id<T>(ST_PHI), s);
+      launch_phi_stage<T>(b, ab_of<T>(h), gbuf, kp, s);
+    }
     StageTimer t(stage_id<T>(ST_LEG_ANALYSIS), s);
     launch_legendre_analysis<T>(b, tb, gbuf, A, kp, s);
   }
   {
     StageTimer t(stage_id<T>(ST_RADIAL_FWD), s);
     launch_radial_forward<T>(b, tb, A, Yin, ldin, Yold, ldold, out, ldout, alpha, c, beta, true,
-                             Zkb, k, kp, s);
+                             Zkb, k, kp, s, A2);
   }
   CES_HIP(hipGetLastError());
   return CES_OK;
@@ -1013,6 +1043,16 @@ ces_status ces_basis_tables(ces_basis bb, double* h_zeros, double* h_radial, dou
   return CES_OK;
 }
 
+namespace {
+// V_eff in the form the angular stage takes (h.ab64, h.ab32).
+void veff_tables(Ham& h, hipStream_t s) {
+  if (h.basis->L <= kFusedL)
+    launch_veff_quadrant(*h.basis, h.veff, h.ab64, h.ab32, s);
+  else
+    launch_veff_fourier(*h.basis, h.veff, h.ab64, h.ab32, s);
+}
+}  // namespace
+
 ces_status ces_ham_create(ces_basis bb, const double* d_veff, int n_proj, const double* d_proj,
                           const double* h_proj_energy, void* stream, ces_ham* out) {
   if (!out) return fail(CES_ERR_INVALID_ARG, "null output handle");
@@ -1029,7 +1069,8 @@ ces_status ces_ham_create(ces_basis bb, const double* d_veff, int n_proj, const 
   h.basis = &b;
   h.n_proj = n_proj;
   const size_t S = 2 * size_t(b.L) - 1;
-  const size_t nab = size_t(b.n_r) * b.n_theta * 2 * S;
+  const size_t nab =
+      size_t(b.n_r) * b.n_theta * (b.L <= kFusedL ? 64 : 2 * S);
   const size_t sz_v = align256(size_t(b.n_grid) * 8), sz_ab64 = align256(nab * 8),
                sz_ab32 = align256(nab * 4), sz_p64 = align256(size_t(b.d) * n_proj * 8),
                sz_p32 = align256(size_t(f32_ld(b.d)) * n_proj * 4), sz_h = align256(size_t(n_proj) * 8) + align256(size_t(n_proj) * 4);
@@ -1066,7 +1107,7 @@ ces_status ces_ham_create(ces_basis bb, const double* d_veff, int n_proj, const 
     return cleanup(st);
   if (hipMemcpyAsync(h.veff, d_veff, size_t(b.n_grid) * 8, hipMemcpyDeviceToDevice, s) != hipSuccess)
     return cleanup(fail(CES_ERR_DEVICE, "copy of V_eff failed"));
-  launch_veff_fourier(b, h.veff, h.ab64, h.ab32, s);
+  veff_tables(h, s);
   if (n_proj > 0) {
     if (hipMemcpyAsync(h.proj64, d_proj, size_t(b.d) * n_proj * 8, hipMemcpyDeviceToDevice, s) !=
         hipSuccess)
@@ -1095,7 +1136,7 @@ ces_status ces_ham_set_veff(ces_ham hh, const double* d_veff, void* stream) {
   Ham& h = hh->h;
   hipStream_t s = static_cast<hipStream_t>(stream);
   CES_HIP(hipMemcpyAsync(h.veff, d_veff, size_t(h.basis->n_grid) * 8, hipMemcpyDeviceToDevice, s));
-  launch_veff_fourier(*h.basis, h.veff, h.ab64, h.ab32, s);
+  veff_tables(h, s);
   CES_HIP(hipGetLastError());
   return CES_OK;
 }

@@ -38,6 +38,14 @@ struct DevTables {
   T* PwT = nullptr;    // [m][J4][L16]   w_j * Pm[m][m + ll][j] at [m][j][ll]
 };
 
+// MFMA operand tables of the fused angular stage (kernels_fused.hip)
+template <typename T>
+struct FusedTables {
+  T* T12 = nullptr;
+  T* PA = nullptr;
+  T* PC = nullptr;
+};
+
 struct Basis {
   int L = 0, N = 0, n_r = 0, n_theta = 0, n_phi = 0, rule = 0;
   double R = 0;
@@ -59,6 +67,9 @@ struct Basis {
   double* dev_trig_a = nullptr;    // analysis
   double* dev_trig_s64 = nullptr;  // synthesis, FP64 and FP32
   float* dev_trig_s32 = nullptr;
+  FusedTables<double> f64;         // L <= kFusedL only
+  FusedTables<float> f32;
+  double* dev_dir = nullptr;       // V_eff onto the fused stage's phi points
   double* dev_rnode = nullptr;   // [n_r] radial nodes
   double* dev_wr = nullptr;      // [n_r] radial weights (r^2 included)
   double* dev_cth = nullptr;     // [n_theta] cos(theta_j)
@@ -73,7 +84,10 @@ struct Basis {
 struct Ham {
   Basis* basis = nullptr;
   double* veff = nullptr;   // [n_grid]
-  double* ab64 = nullptr;   // [n_r*n_theta*2*S]
+  // V_eff as the angular stage takes it: halved phi-Fourier sums
+  // [n_r*n_theta*2*S], or with L <= kFusedL its values on the fused stage's
+  // points [n_r*n_theta][image][point]
+  double* ab64 = nullptr;
   float* ab32 = nullptr;
   int n_proj = 0;
   double* proj64 = nullptr; // d x n_proj
@@ -181,15 +195,34 @@ void launch_radial_inverse(const Basis& b, const DevTables<T>& tb, const T* X, i
                            T* G, int k, int kp, hipStream_t s);
 
 // out = alpha * (Z + lamh o Yin + KB - c * Yin) + beta * Yold, with
-// Z = Rfwd^T A (per lm) (+ Zkb, the projector term: column-major d x k, ld d,
+// Z = Rfwd^T (A [+ A2, n_r <= kOneChunkNodes only]) (per lm) (+ Zkb, the projector term: column-major d x k, ld d,
 // or null).  Yold may be null when beta == 0.
 template <typename T>
 void launch_radial_forward(const Basis& b, const DevTables<T>& tb, const T* A, const T* Yin,
                            int64_t ldin, const T* Yold, int64_t ldold, T* out, int64_t ldout,
                            T alpha, T cshift, T beta, bool kinetic, const T* Zkb, int k, int kp,
-                           hipStream_t s);
+                           hipStream_t s, const T* A2 = nullptr);
 
-// Angular stage on MFMA: G -> gbuf (n_r x n_theta x S x kp) -> gh (in place)
+// Fused angular stage G -> A for L <= kFusedL (kernels_fused.hip).
+constexpr int kFusedL = 16;
+// Largest n_r whose radial forward contraction is loaded at once (and which
+// may take A in two parts).
+constexpr int kOneChunkNodes = 96;
+struct FusedShape {
+  int kc, ngrp, th;
+};
+FusedShape fused_shape(const Basis& b);
+void fused_tables(const Basis& b, bool f32, std::vector<double>& t12, std::vector<double>& pa,
+                  std::vector<double>& pc, std::vector<double>& dir);
+void launch_veff_quadrant(const Basis& b, const double* V, double* v64, float* v32,
+                          hipStream_t s);
+int fused_parts(const Basis& b, int kp, size_t room);
+template <typename T>
+void launch_angular_fused(const Basis& b, const FusedTables<T>& tb, const T* V4, const T* G, T* A0,
+                          T* A1, int parts, int kp, hipStream_t s);
+
+// Angular stage on MFMA (L > kFusedL, and the transforms that stop at or
+// start from g): G -> gbuf (n_r x n_theta x S x kp) -> gh (in place)
 // -> A, as three launches.  n_r: radial nodes of the buffers (0: the basis's).
 template <typename T>
 void launch_legendre_synth(const Basis& b, const DevTables<T>& tb, const T* G, T* gbuf, int kp,

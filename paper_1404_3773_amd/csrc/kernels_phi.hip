@@ -269,8 +269,8 @@ __global__ __launch_bounds__(256) void k_density(const T* __restrict__ g,
   if (row < n_rows) load_slots<T, KT>(g + row * rstride + l16, kp, L, kk, c, s);
   const T* tab = tb;
   if constexpr (TL) {
-    T* tl = reinterpret_cast<T*>(reinterpret_cast<double*>(smem_raw) + 4 * n);
-    for (int e = threadIdx.x; e < npt * KT * 2 * 64; e += 256) tl[e] = tb[e];
+    T* tl = reinterpret_cast<T*>(reinterpret_cast<double*>(smem_raw) + 4 * n);   // 32-byte aligned
+    copy_to_lds<256>(tb, tl, npt * KT * 2 * 64);
     __syncthreads();   // the only barrier
     tab = tl;
   }

@@ -177,9 +177,11 @@ void k_radial_inverse_mfma(const T* __restrict__ RiT,
 // Column tile nt of lane l16 is column 2 l16 + nt of the 32 (one 8-byte load
 // of the streamed operand per k-step), so result row q of tile nt is column
 // 2 q + nt.
-template <typename T, int MT, int CK, bool ONE>
+// TWO: A comes in two parts (A2 the second), added as they are loaded.
+template <typename T, int MT, int CK, bool ONE, bool TWO>
 __global__ __launch_bounds__(256) void k_radial_forward_mfma(
-    const T* __restrict__ RfT, const T* __restrict__ A, const T* __restrict__ lamh,
+    const T* __restrict__ RfT, const T* __restrict__ A, const T* __restrict__ A2,
+    const T* __restrict__ lamh,
     const T* __restrict__ Yin, int64_t ldin, const T* __restrict__ Yold, int64_t ldold,
     T* __restrict__ out, int64_t ldout, T alpha, T cshift, T beta, int kinetic,
     const T* __restrict__ Zkb, const int* __restrict__ lay, int64_t d, int L, int N, int n_r,
@@ -215,6 +217,8 @@ __global__ __launch_bounds__(256) void k_radial_forward_mfma(
     for (int nt = 0; nt < RI_NT; ++nt) acc[u][nt] = zero_acc<acc_t>();
   const T* Rl = RfT + static_cast<int64_t>(l) * R4 * N16 + l16;
   const T* Ab = A + static_cast<int64_t>(lm) * kp + i0 + cl;
+  static_assert(ONE || !TWO, "the second part is taken by the one-chunk form");
+  T b2[TWO ? CK : 1][RI_NT];
   const int64_t rstride = static_cast<int64_t>(L) * L * kp;
   // operands in chunks of CK k-steps (4 CK radial nodes)
   auto load = [&](int chunk, T (*a)[MT], T (*b)[RI_NT]) __attribute__((always_inline)) {
@@ -228,6 +232,8 @@ __global__ __launch_bounds__(256) void k_radial_forward_mfma(
 #pragma unroll
       for (int u = 0; u < MT; ++u) a[t][u] = Rl[static_cast<int64_t>(rt) * N16 + mrow[u]];
       load_vec<T, RI_NT>(Ab + roff, b[t]);
+      if constexpr (TWO)
+        load_vec<T, RI_NT>(A2 + static_cast<int64_t>(lm) * kp + i0 + cl + roff, b2[t]);
     }
   };
   // transposed product Z^T = A^T Rf: the streamed A block is the MFMA A
@@ -285,7 +291,13 @@ __global__ __launch_bounds__(256) void k_radial_forward_mfma(
   __builtin_amdgcn_sched_barrier(0);   // issue every load of the chunk before the first MFMA
   if constexpr (ONE) {      // whole contraction in one chunk (R4 <= 4 CK; rows past R4 are zero)
 #pragma unroll
-    for (int t = 0; t < CK; ++t) step(4 * t + kk, ca[t], cb[t]);
+    for (int t = 0; t < CK; ++t) {
+      if constexpr (TWO) {
+#pragma unroll
+        for (int nt = 0; nt < RI_NT; ++nt) cb[t][nt] += b2[t][nt];
+      }
+      step(4 * t + kk, ca[t], cb[t]);
+    }
   } else {
     const int nch = (R4 + 4 * CK - 1) / (4 * CK);
     T na[CK][MT], nb[CK][RI_NT];
@@ -379,24 +391,23 @@ void launch_radial_inverse(const Basis& b, const DevTables<T>& tb, const T* X, i
   radial_inverse_ck<T, kStreamCK, false>(b, tb, X, ldx, G, k, kp, s);
 }
 
-template <typename T, int CK, bool ONE>
-void radial_forward_ck(const Basis& b, const DevTables<T>& tb, const T* A, const T* Yin,
-                       int64_t ldin, const T* Yold, int64_t ldold, T* out, int64_t ldout,
-                       T alpha, T cshift, T beta, bool kinetic, const T* Zkb, int k, int kp,
-                       hipStream_t s) {
+template <typename T, int CK, bool ONE, bool TWO>
+void radial_forward_ck(const Basis& b, const DevTables<T>& tb, const T* A, const T* A2,
+                       const T* Yin, int64_t ldin, const T* Yold, int64_t ldold, T* out,
+                       int64_t ldout, T alpha, T cshift, T beta, bool kinetic, const T* Zkb, int k,
+                       int kp, hipStream_t s) {
   dim3 grid((k + 16 * RI_NT - 1) / (16 * RI_NT), b.L * b.L);
   const int mt = (rup(b.N, 16) / 16 + 3) / 4;   // N <= 192: at most 3 tiles per wave
   const int kin = kinetic ? 1 : 0;
+  auto go = [&](auto mt_tag) {
+    k_radial_forward_mfma<T, decltype(mt_tag)::value, CK, ONE, TWO><<<grid, 256, 0, s>>>(
+        tb.RfT, A, A2, tb.lamh, Yin, ldin, Yold, ldold, out, ldout, alpha, cshift, beta, kin, Zkb,
+        b.dev_lay, b.d, b.L, b.N, b.n_r, k, kp);
+  };
   switch (mt) {
-    case 1: k_radial_forward_mfma<T, 1, CK, ONE><<<grid, 256, 0, s>>>(tb.RfT, A, tb.lamh, Yin, ldin, Yold, ldold, out,
-                                                    ldout, alpha, cshift, beta, kin, Zkb, b.dev_lay, b.d, b.L, b.N,
-                                                    b.n_r, k, kp); break;
-    case 2: k_radial_forward_mfma<T, 2, CK, ONE><<<grid, 256, 0, s>>>(tb.RfT, A, tb.lamh, Yin, ldin, Yold, ldold, out,
-                                                    ldout, alpha, cshift, beta, kin, Zkb, b.dev_lay, b.d, b.L, b.N,
-                                                    b.n_r, k, kp); break;
-    default: k_radial_forward_mfma<T, 3, CK, ONE><<<grid, 256, 0, s>>>(tb.RfT, A, tb.lamh, Yin, ldin, Yold, ldold, out,
-                                                     ldout, alpha, cshift, beta, kin, Zkb, b.dev_lay, b.d, b.L, b.N,
-                                                     b.n_r, k, kp); break;
+    case 1: go(std::integral_constant<int, 1>()); break;
+    case 2: go(std::integral_constant<int, 2>()); break;
+    default: go(std::integral_constant<int, 3>()); break;
   }
 }
 
@@ -404,19 +415,21 @@ template <typename T>
 void launch_radial_forward(const Basis& b, const DevTables<T>& tb, const T* A, const T* Yin,
                            int64_t ldin, const T* Yold, int64_t ldold, T* out, int64_t ldout,
                            T alpha, T cshift, T beta, bool kinetic, const T* Zkb, int k, int kp,
-                           hipStream_t s) {
+                           hipStream_t s, const T* A2) {
   const int ks = rup(b.n_r, 4) / 4;   // k-steps of the contraction over r
-  if (ks <= 8)
-    return radial_forward_ck<T, 8, true>(b, tb, A, Yin, ldin, Yold, ldold, out, ldout, alpha, cshift,
-                                   beta, kinetic, Zkb, k, kp, s);
-  if (ks <= 16)
-    return radial_forward_ck<T, 16, true>(b, tb, A, Yin, ldin, Yold, ldold, out, ldout, alpha, cshift,
-                                    beta, kinetic, Zkb, k, kp, s);
-  if (ks <= 24)
-    return radial_forward_ck<T, 24, true>(b, tb, A, Yin, ldin, Yold, ldold, out, ldout, alpha, cshift,
-                                    beta, kinetic, Zkb, k, kp, s);
-  radial_forward_ck<T, kStreamCK, false>(b, tb, A, Yin, ldin, Yold, ldold, out, ldout, alpha, cshift, beta,
-                          kinetic, Zkb, k, kp, s);
+  auto go = [&](auto ck, auto one, auto two) {
+    radial_forward_ck<T, decltype(ck)::value, decltype(one)::value, decltype(two)::value>(
+        b, tb, A, A2, Yin, ldin, Yold, ldold, out, ldout, alpha, cshift, beta, kinetic, Zkb, k, kp,
+        s);
+  };
+  auto one = [&](auto ck) {
+    A2 ? go(ck, std::true_type(), std::true_type()) : go(ck, std::true_type(), std::false_type());
+  };
+  static_assert(4 * 24 == kOneChunkNodes, "the longest one-chunk form");
+  if (ks <= 8) return one(std::integral_constant<int, 8>());
+  if (ks <= 16) return one(std::integral_constant<int, 16>());
+  if (ks <= 24) return one(std::integral_constant<int, 24>());
+  go(std::integral_constant<int, kStreamCK>(), std::false_type(), std::false_type());
 }
 
 #define CES_INST(T)                                                                           \
@@ -424,7 +437,7 @@ void launch_radial_forward(const Basis& b, const DevTables<T>& tb, const T* A, c
                                          T*, int, int, hipStream_t);                          \
   template void launch_radial_forward<T>(const Basis&, const DevTables<T>&, const T*, const T*, \
                                          int64_t, const T*, int64_t, T*, int64_t, T, T, T, bool, \
-                                         const T*, int, int, hipStream_t);
+                                         const T*, int, int, hipStream_t, const T*);
 CES_INST(float)
 CES_INST(double)
 #undef CES_INST

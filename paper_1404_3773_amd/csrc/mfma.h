@@ -64,6 +64,25 @@ __device__ __forceinline__ void store_vec(T* p, const T (&in)[N]) {
     *reinterpret_cast<vt*>(p) = x;
 }
 
+// n elements (a multiple of 16 bytes; both arrays 16-byte aligned) from
+// global memory to LDS by the workgroup's NT threads, eight 16-byte loads in
+// flight per thread: a plain copy loop waits for every load (32 KB by 256
+// threads: 14,000 cycles).
+template <int NT, typename T>
+__device__ __forceinline__ void copy_to_lds(const T* __restrict__ src, T* lds, int n) {
+  const uint4* s = reinterpret_cast<const uint4*>(src);
+  uint4* d = reinterpret_cast<uint4*>(lds);
+  const int m = n / static_cast<int>(16 / sizeof(T));
+  for (int e0 = threadIdx.x; e0 < m; e0 += 8 * NT) {
+    uint4 x[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) x[u] = s[min(e0 + u * NT, m - 1)];
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (e0 + u * NT < m) d[e0 + u * NT] = x[u];
+  }
+}
+
 template <typename A>
 __device__ __forceinline__ A zero_acc() {
   A z;
