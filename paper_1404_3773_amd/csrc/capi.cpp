@@ -479,9 +479,9 @@ const float* ab_of<float>(const Ham& h) { return h.ab32; }
 // out = alpha * (H Yin - c Yin) + beta * Yold  (kinetic and projector terms
 // included) for k columns with kp = k rounded up to 16.  Uses the G, A, gbuf
 // and projector regions of the workspace.
-template <typename T>
+template <typename T, typename TO>
 ces_status h_step_block(Ham& h, const Layout& ly, void* work, int k, const T* Yin, int64_t ldin,
-                        const T* Yold, int64_t ldold, T* out, int64_t ldout, T alpha, T c,
+                        const T* Yold, int64_t ldold, TO* out, int64_t ldout, T alpha, T c,
                         T beta, hipStream_t s) {
   const Basis& b = *h.basis;
   const DevTables<T>& tb = tables<T>(b);
@@ -531,8 +531,8 @@ ces_status h_step_block(Ham& h, const Layout& ly, void* work, int k, const T* Yi
   }
   {
     StageTimer t(stage_id<T>(ST_RADIAL_FWD), s);
-    launch_radial_forward<T>(b, tb, A, Yin, ldin, Yold, ldold, out, ldout, alpha, c, beta, true,
-                             Zkb, k, kp, s, A2);
+    launch_radial_forward<T, TO>(b, tb, A, Yin, ldin, Yold, ldold, out, ldout, alpha, c, beta,
+                                 true, Zkb, k, kp, s, A2);
   }
   CES_HIP(hipGetLastError());
   return CES_OK;
@@ -541,27 +541,30 @@ ces_status h_step_block(Ham& h, const Layout& ly, void* work, int k, const T* Yi
 // h_step_block over column chunks of at most the columns the layout's G, A
 // and gbuf hold in this precision (one chunk unless an FP64 product runs in a
 // mixed-precision workspace).
-template <typename T>
+template <typename T, typename TO>
 ces_status h_step(Ham& h, const Layout& ly, void* work, int k, const T* Yin, int64_t ldin,
-                  const T* Yold, int64_t ldold, T* out, int64_t ldout, T alpha, T c, T beta,
+                  const T* Yold, int64_t ldold, TO* out, int64_t ldout, T alpha, T c, T beta,
                   hipStream_t s) {
   const int64_t cap = sizeof(T) == 8 ? ly.kc64 : ly.kp;
   if (cap < kColPad) return fail(CES_ERR_WORKSPACE, "workspace holds no product of this precision");
   for (int64_t c0 = 0; c0 < k; c0 += cap) {
     const int kc = static_cast<int>(std::min<int64_t>(cap, k - c0));
-    CES_TRY(h_step_block<T>(h, ly, work, kc, Yin + c0 * ldin, ldin,
-                            Yold ? Yold + c0 * ldold : nullptr, ldold, out + c0 * ldout, ldout,
-                            alpha, c, beta, s));
+    CES_TRY((h_step_block<T, TO>(h, ly, work, kc, Yin + c0 * ldin, ldin,
+                                 Yold ? Yold + c0 * ldold : nullptr, ldold, out + c0 * ldout,
+                                 ldout, alpha, c, beta, s)));
   }
   return CES_OK;
 }
 
-template ces_status h_step<double>(Ham&, const Layout&, void*, int, const double*, int64_t,
-                                   const double*, int64_t, double*, int64_t, double, double,
-                                   double, hipStream_t);
-template ces_status h_step<float>(Ham&, const Layout&, void*, int, const float*, int64_t,
-                                  const float*, int64_t, float*, int64_t, float, float, float,
-                                  hipStream_t);
+template ces_status h_step<double, double>(Ham&, const Layout&, void*, int, const double*, int64_t,
+                                           const double*, int64_t, double*, int64_t, double,
+                                           double, double, hipStream_t);
+template ces_status h_step<float, float>(Ham&, const Layout&, void*, int, const float*, int64_t,
+                                         const float*, int64_t, float*, int64_t, float, float,
+                                         float, hipStream_t);
+template ces_status h_step<float, double>(Ham&, const Layout&, void*, int, const float*, int64_t,
+                                          const float*, int64_t, double*, int64_t, float, float,
+                                          float, hipStream_t);
 
 // Y = H X on the regions of `ly` in `work` (FP64, or FP32 with the
 // conversions of the mixed precision).
@@ -569,15 +572,11 @@ ces_status apply_H_impl(Ham& h, const Layout& ly, void* work, int k, const doubl
                         int64_t ldx, double* Y, int64_t ldy, int prec, hipStream_t s) {
   const int64_t d = h.basis->d;
   if (prec == CES_PREC_FP64)
-    return h_step<double>(h, ly, work, k, X, ldx, nullptr, 0, Y, ldy, 1.0, 0.0, 0.0, s);
+    return h_step<double, double>(h, ly, work, k, X, ldx, nullptr, 0, Y, ldy, 1.0, 0.0, 0.0, s);
   float* F0 = Ptr<float>::at(work, ly.F0);
-  float* F1 = Ptr<float>::at(work, ly.F1);
   const int64_t ldf = f32_ld(d);
   launch_convert<double, float>(X, ldx, F0, ldf, d, k, s);
-  CES_TRY(h_step<float>(h, ly, work, k, F0, ldf, nullptr, 0, F1, ldf, 1.0f, 0.0f, 0.0f, s));
-  launch_convert<float, double>(F1, ldf, Y, ldy, d, k, s);
-  CES_HIP(hipGetLastError());
-  return CES_OK;
+  return h_step<float, double>(h, ly, work, k, F0, ldf, nullptr, 0, Y, ldy, 1.0f, 0.0f, 0.0f, s);
 }
 
 ces_status check_ham(ces_ham hh) {
@@ -636,15 +635,20 @@ ces_status check_work_for(Ham& h, int k, int prec, void* work, size_t bytes, Lay
   return check_work(h, k, prec, work, bytes, ly);
 }
 
-// Chebyshev filter on an internal block; Y0 (ld ld0) in place.
+// Chebyshev filter: Y0 (ld ld0) and Yb hold the recurrence, the last step
+// writes X (which may be Y0).
 template <typename T>
 ces_status cheb_run(Ham& h, const Layout& ly, void* work, int k, T* Y0, int64_t ld0, T* Yb,
-                    int64_t ldb, int degree, double a, double bnd, double a0, hipStream_t s,
-                    T** result, int64_t* ldres) {
+                    int64_t ldb, double* X, int64_t ldx, int degree, double a, double bnd,
+                    double a0, hipStream_t s) {
   const double e = (bnd - a) / 2.0, c = (bnd + a) / 2.0;
   const double sigma1 = e / (a0 - c);
   // step 1: Yb = (sigma1/e) (H Y0 - c Y0)
-  CES_TRY(h_step<T>(h, ly, work, k, Y0, ld0, nullptr, 0, Yb, ldb, T(sigma1 / e), T(c), T(0), s));
+  if (degree == 1)
+    return h_step<T, double>(h, ly, work, k, Y0, ld0, nullptr, 0, X, ldx, T(sigma1 / e), T(c),
+                             T(0), s);
+  CES_TRY((h_step<T, T>(h, ly, work, k, Y0, ld0, nullptr, 0, Yb, ldb, T(sigma1 / e), T(c), T(0),
+                        s)));
   T* cur = Yb;
   int64_t ldc = ldb;
   T* prev = Y0;
@@ -652,15 +656,17 @@ ces_status cheb_run(Ham& h, const Layout& ly, void* work, int k, T* Y0, int64_t 
   double sigma = sigma1;
   for (int j = 2; j <= degree; ++j) {
     const double sn = 1.0 / (2.0 / sigma1 - sigma);
-    // Y_j = (2 sn / e)(H Y_{j-1} - c Y_{j-1}) - sigma sn Y_{j-2}, written over Y_{j-2}
-    CES_TRY(h_step<T>(h, ly, work, k, cur, ldc, prev, ldp, prev, ldp, T(2.0 * sn / e), T(c),
-                      T(-sigma * sn), s));
+    // Y_j = (2 sn / e)(H Y_{j-1} - c Y_{j-1}) - sigma sn Y_{j-2}, written over
+    // Y_{j-2} (the last one into X)
+    if (j == degree)
+      return h_step<T, double>(h, ly, work, k, cur, ldc, prev, ldp, X, ldx, T(2.0 * sn / e), T(c),
+                               T(-sigma * sn), s);
+    CES_TRY((h_step<T, T>(h, ly, work, k, cur, ldc, prev, ldp, prev, ldp, T(2.0 * sn / e), T(c),
+                          T(-sigma * sn), s)));
     std::swap(cur, prev);
     std::swap(ldc, ldp);
     sigma = sn;
   }
-  *result = cur;
-  *ldres = ldc;
   return CES_OK;
 }
 
@@ -770,14 +776,14 @@ ces_status rr_locked(Ham& h, const Layout& ly, void* work, int k, double* X, int
     double* HQ = HX ? HX : B1;
     const int64_t ldhq = HX ? ldhx : d;
     if (hx_prec == CES_PREC_FP64) {
-      CES_TRY(h_step<double>(h, ly, work, k, X, ldx, nullptr, 0, HQ, ldhq, 1.0, 0.0, 0.0, s));
+      CES_TRY((h_step<double, double>(h, ly, work, k, X, ldx, nullptr, 0, HQ, ldhq, 1.0, 0.0, 0.0,
+                                      s)));
     } else {
       float* F0 = Ptr<float>::at(work, ly.F0);
-      float* F1 = Ptr<float>::at(work, ly.F1);
       const int64_t ldf = f32_ld(d);
       launch_convert<double, float>(X, ldx, F0, ldf, d, k, s);
-      CES_TRY(h_step<float>(h, ly, work, k, F0, ldf, nullptr, 0, F1, ldf, 1.0f, 0.0f, 0.0f, s));
-      launch_convert<float, double>(F1, ldf, HQ, ldhq, d, k, s);
+      CES_TRY((h_step<float, double>(h, ly, work, k, F0, ldf, nullptr, 0, HQ, ldhq, 1.0f, 0.0f,
+                                     0.0f, s)));
     }
     // Hs = Q^T H Q, eigen-decomposition (ascending)
     launch_gram(X, ldx, HQ, ldhq, S1, part, d, k, s, true);
@@ -1186,20 +1192,14 @@ ces_status ces_cheb_filter(ces_ham hh, int k, double* d_X, int64_t ldx, int degr
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int64_t d = h.basis->d;
   if (prec == CES_PREC_FP64) {
-    double* B1 = Ptr<double>::at(d_work, ly.B1);
-    double* res = nullptr;
-    int64_t ldr = 0;
-    CES_TRY(cheb_run<double>(h, ly, d_work, k, d_X, ldx, B1, d, degree, a, b, a0, s, &res, &ldr));
-    if (res != d_X) launch_copy2d(res, ldr, d_X, ldx, d, k, s);
+    CES_TRY(cheb_run<double>(h, ly, d_work, k, d_X, ldx, Ptr<double>::at(d_work, ly.B1), d, d_X,
+                             ldx, degree, a, b, a0, s));
   } else {
     float* F0 = Ptr<float>::at(d_work, ly.F0);
     float* F1 = Ptr<float>::at(d_work, ly.F1);
     const int64_t ldf = f32_ld(d);
     launch_convert<double, float>(d_X, ldx, F0, ldf, d, k, s);
-    float* res = nullptr;
-    int64_t ldr = 0;
-    CES_TRY(cheb_run<float>(h, ly, d_work, k, F0, ldf, F1, ldf, degree, a, b, a0, s, &res, &ldr));
-    launch_convert<float, double>(res, ldr, d_X, ldx, d, k, s);
+    CES_TRY(cheb_run<float>(h, ly, d_work, k, F0, ldf, F1, ldf, d_X, ldx, degree, a, b, a0, s));
   }
   CES_HIP(hipGetLastError());
   return CES_OK;
@@ -1246,7 +1246,7 @@ ces_status ces_lanczos_bound(ces_ham hh, const double* d_v0, int steps, double* 
   std::vector<double> al, be;
   double beta = 0.0;
   for (int j = 0; j < steps; ++j) {
-    CES_TRY(h_step<double>(h, ly, d_work, 1, v, d, nullptr, 0, w, d, 1.0, 0.0, 0.0, s));
+    CES_TRY((h_step<double, double>(h, ly, d_work, 1, v, d, nullptr, 0, w, d, 1.0, 0.0, 0.0, s)));
     launch_dot(v, w, d, sc, sc + 64, s);
     CES_TRY(stage_read(h, 0, sc, 8, s));
     CES_HIP(hipStreamSynchronize(s));
@@ -1298,21 +1298,14 @@ ces_status ces_chefsi(ces_ham hh, int k, double* d_X, int64_t ldx, int degree, d
     if (!(a < b)) return fail(CES_ERR_INVALID_ARG, "upper bound b is below the Ritz values");
     const double a0u = (a0 < a) ? a0 : a - 1e-6 * std::max(1.0, std::fabs(a));
     if (prec == CES_PREC_FP64) {
-      double* B1 = Ptr<double>::at(d_work, ly.B1);
-      double* out = nullptr;
-      int64_t ldr = 0;
-      CES_TRY(cheb_run<double>(h, ly, d_work, k, d_X, ldx, B1, d, degree, a, b, a0u, s, &out, &ldr));
-      if (out != d_X) launch_copy2d(out, ldr, d_X, ldx, d, k, s);
+      CES_TRY(cheb_run<double>(h, ly, d_work, k, d_X, ldx, Ptr<double>::at(d_work, ly.B1), d, d_X,
+                               ldx, degree, a, b, a0u, s));
     } else {
       float* F0 = Ptr<float>::at(d_work, ly.F0);
       float* F1 = Ptr<float>::at(d_work, ly.F1);
       const int64_t ldf = f32_ld(d);
       launch_convert<double, float>(d_X, ldx, F0, ldf, d, k, s);
-      float* out = nullptr;
-      int64_t ldr = 0;
-      CES_TRY(cheb_run<float>(h, ly, d_work, k, F0, ldf, F1, ldf, degree, a, b, a0u, s, &out,
-                              &ldr));
-      launch_convert<float, double>(out, ldr, d_X, ldx, d, k, s);
+      CES_TRY(cheb_run<float>(h, ly, d_work, k, F0, ldf, F1, ldf, d_X, ldx, degree, a, b, a0u, s));
     }
     theta_old = theta;
     CES_TRY(rr_impl(h, ly, d_work, k, d_X, ldx, nullptr, ldx, d_eval, d_resnorm, CES_PREC_FP64, s,
@@ -1372,7 +1365,7 @@ ces_status ces_from_grid(ces_ham hh, int k, const double* d_f, double* d_X, int6
     const int kp = static_cast<int>(round_up(kc, kColPad));
     launch_phi_analysis_cols(b, d_f + c0 * b.n_grid, b.n_grid, kc, kp, gh, s);
     launch_legendre_analysis<double>(b, b.t64, gh, A, kp, s);
-    launch_radial_forward<double>(b, b.t64, A, nullptr, 0, nullptr, 0, d_X + c0 * ldx, ldx, 1.0,
+    launch_radial_forward<double, double>(b, b.t64, A, nullptr, 0, nullptr, 0, d_X + c0 * ldx, ldx, 1.0,
                                   0.0, 0.0, false, nullptr, kc, kp, s);
   }
   CES_HIP(hipGetLastError());

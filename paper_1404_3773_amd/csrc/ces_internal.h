@@ -157,10 +157,12 @@ ces_status check_block(const Ham& h, int k, const void* X, int64_t ldx, const ch
 // The regions one H*X uses (G, A, gbuf, F0/F1 in mixed precision, projector
 // products), sized for the precision the product runs in.
 Layout hx_layout(const Ham& h, int k, int prec);
-// out = alpha (H Yin - c Yin) + beta Yold on the regions of ly in work.
-template <typename T>
+// out = alpha (H Yin - c Yin) + beta Yold on the regions of ly in work,
+// computed in T and stored as TO (T, or double for T = float).  out may be
+// Yold or Yin (every value is read by the thread that replaces it).
+template <typename T, typename TO>
 ces_status h_step(Ham& h, const Layout& ly, void* work, int k, const T* Yin, int64_t ldin,
-                  const T* Yold, int64_t ldold, T* out, int64_t ldout, T alpha, T c, T beta,
+                  const T* Yold, int64_t ldold, TO* out, int64_t ldout, T alpha, T c, T beta,
                   hipStream_t s);
 // Y = H X (FP64, or the mixed-precision conversions around an FP32 product).
 ces_status apply_H_impl(Ham& h, const Layout& ly, void* work, int k, const double* X,
@@ -197,9 +199,9 @@ void launch_radial_inverse(const Basis& b, const DevTables<T>& tb, const T* X, i
 // out = alpha * (Z + lamh o Yin + KB - c * Yin) + beta * Yold, with
 // Z = Rfwd^T (A [+ A2, n_r <= kOneChunkNodes only]) (per lm) (+ Zkb, the projector term: column-major d x k, ld d,
 // or null).  Yold may be null when beta == 0.
-template <typename T>
+template <typename T, typename TO>
 void launch_radial_forward(const Basis& b, const DevTables<T>& tb, const T* A, const T* Yin,
-                           int64_t ldin, const T* Yold, int64_t ldold, T* out, int64_t ldout,
+                           int64_t ldin, const T* Yold, int64_t ldold, TO* out, int64_t ldout,
                            T alpha, T cshift, T beta, bool kinetic, const T* Zkb, int k, int kp,
                            hipStream_t s, const T* A2 = nullptr);
 

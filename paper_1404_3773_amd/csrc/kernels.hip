@@ -339,7 +339,5 @@ void launch_axpby(double a, const double* x, double b, double* y, int64_t n, hip
 
 template void launch_convert<double, float>(const double*, int64_t, float*, int64_t, int64_t,
                                             int, hipStream_t);
-template void launch_convert<float, double>(const float*, int64_t, double*, int64_t, int64_t,
-                                            int, hipStream_t);
 
 }  // namespace ces

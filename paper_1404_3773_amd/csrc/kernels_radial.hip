@@ -178,12 +178,15 @@ void k_radial_inverse_mfma(const T* __restrict__ RiT,
 // of the streamed operand per k-step), so result row q of tile nt is column
 // 2 q + nt.
 // TWO: A comes in two parts (A2 the second), added as they are loaded.
-template <typename T, int MT, int CK, bool ONE, bool TWO>
+// TO: an FP32 product whose result is wanted in FP64 is stored as FP64 at
+// once, not converted in a further pass over it (147 atoms, k = 400: 1332 us
+// here + 532 us there -> 1450 us; 309 atoms, k = 500: 4158 + 1472 -> 4572 us).
+template <typename T, typename TO, int MT, int CK, bool ONE, bool TWO>
 __global__ __launch_bounds__(256) void k_radial_forward_mfma(
     const T* __restrict__ RfT, const T* __restrict__ A, const T* __restrict__ A2,
     const T* __restrict__ lamh,
     const T* __restrict__ Yin, int64_t ldin, const T* __restrict__ Yold, int64_t ldold,
-    T* __restrict__ out, int64_t ldout, T alpha, T cshift, T beta, int kinetic,
+    TO* __restrict__ out, int64_t ldout, T alpha, T cshift, T beta, int kinetic,
     const T* __restrict__ Zkb, const int* __restrict__ lay, int64_t d, int L, int N, int n_r,
     int k, int kp) {
   typedef typename MF<T>::acc acc_t;
@@ -349,7 +352,7 @@ __global__ __launch_bounds__(256) void k_radial_forward_mfma(
         T val = alpha * z;
         if (beta != T(0))
           val += beta * (EPR ? yold[u][nt][v * EPR] : Yold[static_cast<int64_t>(i) * ldold + row]);
-        out[static_cast<int64_t>(i) * ldout + row] = val;
+        out[static_cast<int64_t>(i) * ldout + row] = static_cast<TO>(val);
       }
     }
   }
@@ -391,16 +394,16 @@ void launch_radial_inverse(const Basis& b, const DevTables<T>& tb, const T* X, i
   radial_inverse_ck<T, kStreamCK, false>(b, tb, X, ldx, G, k, kp, s);
 }
 
-template <typename T, int CK, bool ONE, bool TWO>
+template <typename T, typename TO, int CK, bool ONE, bool TWO>
 void radial_forward_ck(const Basis& b, const DevTables<T>& tb, const T* A, const T* A2,
-                       const T* Yin, int64_t ldin, const T* Yold, int64_t ldold, T* out,
+                       const T* Yin, int64_t ldin, const T* Yold, int64_t ldold, TO* out,
                        int64_t ldout, T alpha, T cshift, T beta, bool kinetic, const T* Zkb, int k,
                        int kp, hipStream_t s) {
   dim3 grid((k + 16 * RI_NT - 1) / (16 * RI_NT), b.L * b.L);
   const int mt = (rup(b.N, 16) / 16 + 3) / 4;   // N <= 192: at most 3 tiles per wave
   const int kin = kinetic ? 1 : 0;
   auto go = [&](auto mt_tag) {
-    k_radial_forward_mfma<T, decltype(mt_tag)::value, CK, ONE, TWO><<<grid, 256, 0, s>>>(
+    k_radial_forward_mfma<T, TO, decltype(mt_tag)::value, CK, ONE, TWO><<<grid, 256, 0, s>>>(
         tb.RfT, A, A2, tb.lamh, Yin, ldin, Yold, ldold, out, ldout, alpha, cshift, beta, kin, Zkb,
         b.dev_lay, b.d, b.L, b.N, b.n_r, k, kp);
   };
@@ -411,14 +414,14 @@ void radial_forward_ck(const Basis& b, const DevTables<T>& tb, const T* A, const
   }
 }
 
-template <typename T>
+template <typename T, typename TO>
 void launch_radial_forward(const Basis& b, const DevTables<T>& tb, const T* A, const T* Yin,
-                           int64_t ldin, const T* Yold, int64_t ldold, T* out, int64_t ldout,
+                           int64_t ldin, const T* Yold, int64_t ldold, TO* out, int64_t ldout,
                            T alpha, T cshift, T beta, bool kinetic, const T* Zkb, int k, int kp,
                            hipStream_t s, const T* A2) {
   const int ks = rup(b.n_r, 4) / 4;   // k-steps of the contraction over r
   auto go = [&](auto ck, auto one, auto two) {
-    radial_forward_ck<T, decltype(ck)::value, decltype(one)::value, decltype(two)::value>(
+    radial_forward_ck<T, TO, decltype(ck)::value, decltype(one)::value, decltype(two)::value>(
         b, tb, A, A2, Yin, ldin, Yold, ldold, out, ldout, alpha, cshift, beta, kinetic, Zkb, k, kp,
         s);
   };
@@ -434,12 +437,18 @@ void launch_radial_forward(const Basis& b, const DevTables<T>& tb, const T* A, c
 
 #define CES_INST(T)                                                                           \
   template void launch_radial_inverse<T>(const Basis&, const DevTables<T>&, const T*, int64_t, \
-                                         T*, int, int, hipStream_t);                          \
-  template void launch_radial_forward<T>(const Basis&, const DevTables<T>&, const T*, const T*, \
-                                         int64_t, const T*, int64_t, T*, int64_t, T, T, T, bool, \
-                                         const T*, int, int, hipStream_t, const T*);
+                                         T*, int, int, hipStream_t);
+#define CES_INST2(T, TO)                                                                      \
+  template void launch_radial_forward<T, TO>(const Basis&, const DevTables<T>&, const T*,      \
+                                             const T*, int64_t, const T*, int64_t, TO*,        \
+                                             int64_t, T, T, T, bool, const T*, int, int,       \
+                                             hipStream_t, const T*);
 CES_INST(float)
 CES_INST(double)
+CES_INST2(float, float)
+CES_INST2(float, double)
+CES_INST2(double, double)
+#undef CES_INST2
 #undef CES_INST
 
 }  // namespace ces

@@ -247,14 +247,11 @@ ces_status ces_lobpcg(ces_ham hh, int k, double* d_X, int64_t ldx, int n_lock, c
     lw.kp = round_up(n, kColPad);
     lw.Cpart = ly.kbpart;
     if (prec == CES_PREC_FP64)
-      return h_step<double>(h, lw, d_work, n, V, d, nullptr, 0, AV, d, 1.0, 0.0, 0.0, s);
+      return h_step<double, double>(h, lw, d_work, n, V, d, nullptr, 0, AV, d, 1.0, 0.0, 0.0, s);
     float* F0 = Ptr<float>::at(d_work, lw.F0);
-    float* F1 = Ptr<float>::at(d_work, lw.F1);
     const int64_t ldf = f32_ld(d);
     launch_convert<double, float>(V, d, F0, ldf, d, n, s);
-    CES_TRY(h_step<float>(h, lw, d_work, n, F0, ldf, nullptr, 0, F1, ldf, 1.0f, 0.0f, 0.0f, s));
-    launch_convert<float, double>(F1, ldf, AV, d, d, n, s);
-    return CES_OK;
+    return h_step<float, double>(h, lw, d_work, n, F0, ldf, nullptr, 0, AV, d, 1.0f, 0.0f, 0.0f, s);
   };
 
   // start: deflate against the constraints, then Rayleigh-Ritz
