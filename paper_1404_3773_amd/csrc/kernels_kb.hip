@@ -56,6 +56,14 @@ struct KbShape<double> {  // wave tile 64 x 32, workgroup 128 x 64, 32 alpha per
 struct KgVec {
   static constexpr int KB = 64, TM = 4, TN = 4;
 };
+// C = P^T Y, FP64, wide tiles (kb_wide64): wave tile 64 x 64, so an operand
+// read from LDS serves four MFMAs instead of two or four; 16 alpha per step
+// (one 128-byte line of a row) in two LDS buffers (73.7 KB, two workgroups per
+// CU) and one barrier a step.  FP64 MFMA bound: 60 of 72.7 TFLOP/s at 309
+// atoms, 1236 projectors, k = 250.
+struct KgWide64 {
+  static constexpr int KB = 16, TM = 4, TN = 4;
+};
 constexpr int kKbPerXcd = 64;   // resident workgroups per XCD (32 CUs, 2 each)
 
 // LDS row pitch of the staged tiles: the MFMA operand reads take 16 rows x 4
@@ -854,6 +862,17 @@ KbGrid kb_split_grid(int n_proj, int k, int64_t d) {
 // 158, 54; 512, k = 512: 716, 706 | 411, 467).
 inline bool kb_split(int n_proj, int k) { return n_proj >= 96 && k > 128; }
 
+// FP64 C = P^T Y on 128 x 128 tiles (KgWide64) for long contractions whose
+// columns fill them as well as 64-wide ones (an even number of 64-column
+// tiles).  C in us, 128 x 64 | 128 x 128 tiles: d = 984,150, 1236 projectors,
+// k = 250: 11,620 | 10,440; d = 162,000, k = 256: 192 projectors 382 | 372, 512
+// 751 | 731; k = 400 (7 tiles against 4): 300 projectors 971 | 1132; below d =
+// 100,000 the shorter chunks' starts outweigh it (d = 12,000, 256 projectors,
+// k = 256: 46 | 52).
+inline bool kb_wide64(int n_proj, int k, int64_t d) {
+  return d >= 100000 && n_proj >= 96 && (k + 63) / 64 % 2 == 0;
+}
+
 }  // namespace
 
 // Split-K partial sums of a product with up to k columns: the chunk count
@@ -870,7 +889,10 @@ size_t kb_partial_bytes(int n_proj, int k, int64_t d) {
                                         kb_split(n_proj, kc) ? kb_split_grid(n_proj, kc, d).nchunk
                                                              : 0})) *
                        sizeof(float);
-    const size_t c64 = size_t(kb_grid<KbShape<double>>(n_proj, kc, d).nchunk) * sizeof(double);
+    const size_t c64 =
+        size_t(std::max(kb_grid<KbShape<double>>(n_proj, kc, d).nchunk,
+                        kb_wide64(n_proj, kc, d) ? kb_grid<KgWide64>(n_proj, kc, d).nchunk : 0)) *
+        sizeof(double);
     most = std::max(most, std::max(c32, c64) * size_t(n_proj) * kp);
     if (kc == k) break;
   }
@@ -932,8 +954,11 @@ void launch_kb_gemm(const T* P, int64_t d, int64_t ldp, const T* Y, int64_t ldy,
     else
       go(KbShape<float>{}, std::true_type{}, std::integral_constant<int, 1>{});
   } else {
-    if (ldp % 2 == 0 && ldy % 2 == 0 && reinterpret_cast<uintptr_t>(P) % 16 == 0 &&
-        reinterpret_cast<uintptr_t>(Y) % 16 == 0)
+    const bool vec = ldp % 2 == 0 && ldy % 2 == 0 && reinterpret_cast<uintptr_t>(P) % 16 == 0 &&
+                     reinterpret_cast<uintptr_t>(Y) % 16 == 0;
+    if (vec && kb_wide64(n_proj, k, d))
+      go(KgWide64{}, std::true_type{}, std::integral_constant<int, 2>{});
+    else if (vec)
       go(KbShape<double>{}, std::false_type{}, std::integral_constant<int, 2>{});
     else
       go(KbShape<double>{}, std::false_type{}, std::integral_constant<int, 1>{});
