@@ -170,18 +170,18 @@ void k_radial_inverse_mfma(const T* __restrict__ RiT,
   }
 }
 
-// Workgroup: one (l, m), 32 columns; M = N split over the 4 waves (MT tiles
-// each, repeated past the last and not stored); K = n_r in chunks of four
+// Workgroup: one (l, m), 16 NT columns; M = N split over the 4 waves (MT tiles
+// each, repeated past the last and not stored); K = n_r in chunks of CK
 // k-steps with the next chunk's operands in flight.  The projector term
 // (column-major d x k, ld d) is added in the epilogue when Zkb is given.
-// Column tile nt of lane l16 is column 2 l16 + nt of the 32 (one 8-byte load
-// of the streamed operand per k-step), so result row q of tile nt is column
-// 2 q + nt.
+// Column tile nt of lane l16 is column NT l16 + nt of them (one vector load of
+// the streamed operand per k-step), so result row q of tile nt is column
+// NT q + nt.
 // TWO: A comes in two parts (A2 the second), added as they are loaded.
 // TO: an FP32 product whose result is wanted in FP64 is stored as FP64 at
 // once, not converted in a further pass over it (147 atoms, k = 400: 1332 us
 // here + 532 us there -> 1450 us; 309 atoms, k = 500: 4158 + 1472 -> 4572 us).
-template <typename T, typename TO, int MT, int CK, bool ONE, bool TWO>
+template <typename T, typename TO, int MT, int NT, int CK, bool ONE, bool TWO>
 __global__ __launch_bounds__(256) void k_radial_forward_mfma(
     const T* __restrict__ RfT, const T* __restrict__ A, const T* __restrict__ A2,
     const T* __restrict__ lamh,
@@ -197,7 +197,7 @@ __global__ __launch_bounds__(256) void k_radial_forward_mfma(
   const int Nl = lay[2 * l + 1];
   if (Nl == 0) return;   // no coefficients for this l
   const int64_t obase = lay[2 * l] + static_cast<int64_t>(lm - l * l) * Nl;
-  const int i0 = blockIdx.x * (16 * RI_NT);
+  const int i0 = blockIdx.x * (16 * NT);
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l16 = lane & 15, kk = lane >> 4;
@@ -210,21 +210,21 @@ __global__ __launch_bounds__(256) void k_radial_forward_mfma(
   // forward 8.6 -> 8.2 ms); FP64 keeps the plain loop (the branch costs the
   // forward kernel a wave per SIMD: 15.7 -> 20.2 ms)
   const bool skip_last = sizeof(T) == 4 && MT > 1 && wave + 4 * (MT - 1) >= nmt;
-  // this lane's column pair, clamped into the block (a ragged last block's
-  // lanes past it load the last pair; their columns are >= kp and not stored)
-  const int cl = min(2 * l16, kp - i0 - 2);
-  acc_t acc[MT][RI_NT];
+  // this lane's NT columns, clamped into the block (a ragged last block's
+  // lanes past it load the last ones; their columns are >= kp and not stored)
+  const int cl = min(NT * l16, kp - i0 - NT);
+  acc_t acc[MT][NT];
 #pragma unroll
   for (int u = 0; u < MT; ++u)
 #pragma unroll
-    for (int nt = 0; nt < RI_NT; ++nt) acc[u][nt] = zero_acc<acc_t>();
+    for (int nt = 0; nt < NT; ++nt) acc[u][nt] = zero_acc<acc_t>();
   const T* Rl = RfT + static_cast<int64_t>(l) * R4 * N16 + l16;
   const T* Ab = A + static_cast<int64_t>(lm) * kp + i0 + cl;
   static_assert(ONE || !TWO, "the second part is taken by the one-chunk form");
-  T b2[TWO ? CK : 1][RI_NT];
+  T b2[TWO ? CK : 1][NT];
   const int64_t rstride = static_cast<int64_t>(L) * L * kp;
   // operands in chunks of CK k-steps (4 CK radial nodes)
-  auto load = [&](int chunk, T (*a)[MT], T (*b)[RI_NT]) __attribute__((always_inline)) {
+  auto load = [&](int chunk, T (*a)[MT], T (*b)[NT]) __attribute__((always_inline)) {
 #pragma unroll
     for (int t = 0; t < CK; ++t) {
       // rows past R4 read row R4 - 1 and are masked where used (a select
@@ -234,9 +234,9 @@ __global__ __launch_bounds__(256) void k_radial_forward_mfma(
       const int64_t roff = static_cast<int64_t>(min(r, n_r - 1)) * rstride;
 #pragma unroll
       for (int u = 0; u < MT; ++u) a[t][u] = Rl[static_cast<int64_t>(rt) * N16 + mrow[u]];
-      load_vec<T, RI_NT>(Ab + roff, b[t]);
+      load_vec<T, NT>(Ab + roff, b[t]);
       if constexpr (TWO)
-        load_vec<T, RI_NT>(A2 + static_cast<int64_t>(lm) * kp + i0 + cl + roff, b2[t]);
+        load_vec<T, NT>(A2 + static_cast<int64_t>(lm) * kp + i0 + cl + roff, b2[t]);
     }
   };
   // transposed product Z^T = A^T Rf: the streamed A block is the MFMA A
@@ -249,31 +249,32 @@ __global__ __launch_bounds__(256) void k_radial_forward_mfma(
       if (u == MT - 1 && skip_last) break;
       const T av = ok ? a[u] : T(0);
 #pragma unroll
-      for (int nt = 0; nt < RI_NT; ++nt) acc[u][nt] = MF<T>::mma(b[nt], av, acc[u][nt]);
+      for (int nt = 0; nt < NT; ++nt) acc[u][nt] = MF<T>::mma(b[nt], av, acc[u][nt]);
     }
   };
-  T ca[CK][MT], cb[CK][RI_NT];
+  T ca[CK][MT], cb[CK][NT];
   load(0, ca, cb);
   // epilogue operands (lanes along n, registers along i), indices clamped
   // into the block, invalid entries not stored: in the one-chunk form they
   // are loaded with the contraction's, so the epilogue waits for nothing new;
-  // in the streamed FP32 form (with the projector term too) they are loaded
-  // with the last chunk, in flight while its MFMAs run (in FP64 the registers
-  // would cost a wave per SIMD, so there they are read in the epilogue)
-  constexpr int EPR = (ONE || sizeof(T) == 4) ? 1 : 0;
-  constexpr int ZP = (!ONE && sizeof(T) == 4) ? 1 : 0;
-  T yin[MT][RI_NT][4 * EPR + 1 - EPR], yold[MT][RI_NT][4 * EPR + 1 - EPR];
-  T zk[MT][RI_NT][4 * ZP + 1 - ZP];
-  auto epi_load = [&](const T* Y, int64_t ld, T (*y)[RI_NT][4 * EPR + 1 - EPR])
+  // in the streamed FP32 form of 32 columns (with the projector term too) they
+  // are loaded with the last chunk, in flight while its MFMAs run (elsewhere
+  // the registers would cost waves, so there they are read in the epilogue)
+  constexpr bool AHEAD = !ONE && sizeof(T) == 4 && NT == RI_NT;
+  constexpr int EPR = ONE || AHEAD ? 1 : 0;
+  constexpr int ZP = AHEAD ? 1 : 0;
+  T yin[MT][NT][4 * EPR + 1 - EPR], yold[MT][NT][4 * EPR + 1 - EPR];
+  T zk[MT][NT][4 * ZP + 1 - ZP];
+  auto epi_load = [&](const T* Y, int64_t ld, T (*y)[NT][4 * EPR + 1 - EPR])
       __attribute__((always_inline)) {
 #pragma unroll
     for (int u = 0; u < MT; ++u) {
       const int64_t row = obase + min(mrow[u] + l16, Nl - 1);
 #pragma unroll
-      for (int nt = 0; nt < RI_NT; ++nt)
+      for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
         for (int v = 0; v < 4 * EPR; ++v)
-          y[u][nt][v] = Y[min(i0 + 2 * MF<T>::row(lane, v) + nt, k - 1) * ld + row];
+          y[u][nt][v] = Y[min(i0 + NT * MF<T>::row(lane, v) + nt, k - 1) * ld + row];
     }
   };
   auto zkb_load = [&]() __attribute__((always_inline)) {
@@ -281,10 +282,11 @@ __global__ __launch_bounds__(256) void k_radial_forward_mfma(
     for (int u = 0; u < MT; ++u) {
       const int64_t row = obase + min(mrow[u] + l16, Nl - 1);
 #pragma unroll
-      for (int nt = 0; nt < RI_NT; ++nt)
+      for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
         for (int v = 0; v < 4 * ZP; ++v)
-          zk[u][nt][v] = Zkb[static_cast<int64_t>(min(i0 + 2 * MF<T>::row(lane, v) + nt, k - 1)) * d + row];
+          zk[u][nt][v] =
+              Zkb[static_cast<int64_t>(min(i0 + NT * MF<T>::row(lane, v) + nt, k - 1)) * d + row];
     }
   };
   if constexpr (ONE) {
@@ -297,13 +299,13 @@ __global__ __launch_bounds__(256) void k_radial_forward_mfma(
     for (int t = 0; t < CK; ++t) {
       if constexpr (TWO) {
 #pragma unroll
-        for (int nt = 0; nt < RI_NT; ++nt) cb[t][nt] += b2[t][nt];
+        for (int nt = 0; nt < NT; ++nt) cb[t][nt] += b2[t][nt];
       }
       step(4 * t + kk, ca[t], cb[t]);
     }
   } else {
     const int nch = (R4 + 4 * CK - 1) / (4 * CK);
-    T na[CK][MT], nb[CK][RI_NT];
+    T na[CK][MT], nb[CK][NT];
     // every chunk but the last is full
     for (int c = 0; c + 1 < nch; ++c) {
       load(c + 1, na, nb);
@@ -314,15 +316,15 @@ __global__ __launch_bounds__(256) void k_radial_forward_mfma(
 #pragma unroll
         for (int u = 0; u < MT; ++u) ca[t][u] = na[t][u];
 #pragma unroll
-        for (int nt = 0; nt < RI_NT; ++nt) cb[t][nt] = nb[t][nt];
+        for (int nt = 0; nt < NT; ++nt) cb[t][nt] = nb[t][nt];
       }
     }
-    if constexpr (EPR) {
+    if constexpr (AHEAD) {
       if (kinetic) epi_load(Yin, ldin, yin);
       if (beta != T(0)) epi_load(Yold, ldold, yold);
       if (Zkb) zkb_load();
+      __builtin_amdgcn_sched_barrier(0);
     }
-    __builtin_amdgcn_sched_barrier(0);
     const int c = nch - 1;
 #pragma unroll
     for (int t = 0; t < CK; ++t) {
@@ -339,11 +341,11 @@ __global__ __launch_bounds__(256) void k_radial_forward_mfma(
     const int64_t row = obase + n;
     const T kin = kinetic ? lamh[static_cast<int64_t>(l) * N + n] - cshift : T(0);
 #pragma unroll
-    for (int nt = 0; nt < RI_NT; ++nt) {
+    for (int nt = 0; nt < NT; ++nt) {
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         // columns past k (among them any clamped onto valid data) are skipped
-        const int i = i0 + 2 * MF<T>::row(lane, v) + nt;
+        const int i = i0 + NT * MF<T>::row(lane, v) + nt;
         if (i >= k) continue;
         T z = acc[u][nt][v];
         if (Zkb) z += ZP ? zk[u][nt][v * ZP] : Zkb[static_cast<int64_t>(i) * d + row];
@@ -362,7 +364,23 @@ __global__ __launch_bounds__(256) void k_radial_forward_mfma(
 
 // Short contractions (N <= 64 for the inverse, n_r <= 96 for the forward)
 // load every operand fragment at once (ONE: one chunk of CK k-steps); longer
-// ones stream chunks of kStreamCK k-steps with the next chunk in flight.
+// ones stream chunks of 1 to kStreamCK k-steps with the next chunk in flight.
+// The streamed forward kernel of a wide block waits on memory more than on the
+// matrix cores (0.56 of the time), so its registers go to waves (5 to 8 per
+// SIMD in FP32, 3 to 5 in FP64, from 3 and 4) and not to longer chunks or
+// epilogue operands loaded ahead, and a workgroup takes 64 columns: the l's
+// table, five times the size of A's 32-column block, is read half as often, A
+// in pieces of 256 bytes or more.  Forward in us, 32 columns and 4 k-steps per
+// chunk | 32 and 1 | 64 and 1 | 64 and 2 (the last three without operands ahead):
+// 147 atoms, k = 400, FP64 1892 | 1698 | 1709 | 1688, FP32 1313 | 1317 | 1153 |
+// 1166; 309 atoms, k = 250, FP64 3013 | 3039 | 3067 | 2749, k = 500, FP32 4072 |
+// 4218 | 3408 | 3357; L = 41, N = 73, 110 nodes, k = 100, FP32 131 | 131 | 116 |
+// 107.  Up to 32 columns FP64 takes 32 and 1 (147 atoms, k = 21: 181 | 171) and
+// FP32, bound by the latency of the few workgroups, stays with 32 and 4 (147
+// atoms, k = 32: 118 | 134), as it does below 2048 workgroups of 64 columns (L
+// = 31, N = 66, 100 nodes, k = 48: 27.8 against 32.0; FP64 there 54 against 50) or
+// where 64-column workgroups pad more than 1/8 (k = 130: 72 against 80).
+constexpr int64_t kWideForwardWgs = 2048;
 constexpr int kStreamCK = 4;
 template <typename T, int CK, bool ONE>
 void radial_inverse_ck(const Basis& b, const DevTables<T>& tb, const T* X, int64_t ldx, T* G,
@@ -394,16 +412,16 @@ void launch_radial_inverse(const Basis& b, const DevTables<T>& tb, const T* X, i
   radial_inverse_ck<T, kStreamCK, false>(b, tb, X, ldx, G, k, kp, s);
 }
 
-template <typename T, typename TO, int CK, bool ONE, bool TWO>
+template <typename T, typename TO, int NT, int CK, bool ONE, bool TWO>
 void radial_forward_ck(const Basis& b, const DevTables<T>& tb, const T* A, const T* A2,
                        const T* Yin, int64_t ldin, const T* Yold, int64_t ldold, TO* out,
                        int64_t ldout, T alpha, T cshift, T beta, bool kinetic, const T* Zkb, int k,
                        int kp, hipStream_t s) {
-  dim3 grid((k + 16 * RI_NT - 1) / (16 * RI_NT), b.L * b.L);
+  dim3 grid((k + 16 * NT - 1) / (16 * NT), b.L * b.L);
   const int mt = (rup(b.N, 16) / 16 + 3) / 4;   // N <= 192: at most 3 tiles per wave
   const int kin = kinetic ? 1 : 0;
   auto go = [&](auto mt_tag) {
-    k_radial_forward_mfma<T, TO, decltype(mt_tag)::value, CK, ONE, TWO><<<grid, 256, 0, s>>>(
+    k_radial_forward_mfma<T, TO, decltype(mt_tag)::value, NT, CK, ONE, TWO><<<grid, 256, 0, s>>>(
         tb.RfT, A, A2, tb.lamh, Yin, ldin, Yold, ldold, out, ldout, alpha, cshift, beta, kin, Zkb,
         b.dev_lay, b.d, b.L, b.N, b.n_r, k, kp);
   };
@@ -420,19 +438,28 @@ void launch_radial_forward(const Basis& b, const DevTables<T>& tb, const T* A, c
                            T alpha, T cshift, T beta, bool kinetic, const T* Zkb, int k, int kp,
                            hipStream_t s, const T* A2) {
   const int ks = rup(b.n_r, 4) / 4;   // k-steps of the contraction over r
-  auto go = [&](auto ck, auto one, auto two) {
-    radial_forward_ck<T, TO, decltype(ck)::value, decltype(one)::value, decltype(two)::value>(
+  auto go = [&](auto nt, auto ck, auto one, auto two) {
+    radial_forward_ck<T, TO, decltype(nt)::value, decltype(ck)::value, decltype(one)::value,
+                      decltype(two)::value>(
         b, tb, A, A2, Yin, ldin, Yold, ldold, out, ldout, alpha, cshift, beta, kinetic, Zkb, k, kp,
         s);
   };
   auto one = [&](auto ck) {
-    A2 ? go(ck, std::true_type(), std::true_type()) : go(ck, std::true_type(), std::false_type());
+    const std::integral_constant<int, RI_NT> nt;
+    A2 ? go(nt, ck, std::true_type(), std::true_type())
+       : go(nt, ck, std::true_type(), std::false_type());
   };
   static_assert(4 * 24 == kOneChunkNodes, "the longest one-chunk form");
   if (ks <= 8) return one(std::integral_constant<int, 8>());
   if (ks <= 16) return one(std::integral_constant<int, 16>());
   if (ks <= 24) return one(std::integral_constant<int, 24>());
-  go(std::integral_constant<int, kStreamCK>(), std::false_type(), std::false_type());
+  const int n32 = (k + 31) / 32, n64 = (k + 63) / 64;
+  if (n32 > 1 && 16 * n64 <= 9 * n32 &&
+      (sizeof(T) == 8 || static_cast<int64_t>(n64) * b.L * b.L >= kWideForwardWgs))
+    return go(std::integral_constant<int, 4>(), std::integral_constant<int, 2>(),
+              std::false_type(), std::false_type());
+  go(std::integral_constant<int, RI_NT>(), std::integral_constant<int, sizeof(T) == 8 ? 1 : kStreamCK>(),
+     std::false_type(), std::false_type());
 }
 
 #define CES_INST(T)                                                                           \
