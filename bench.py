@@ -42,6 +42,7 @@ import synth_inputs as si  # noqa: E402
 
 PEAK_FP32 = 157.3e12   # MI355X FP32: vector (256 CUs x 2.4 GHz) = dense matrix, FLOP/s
 PEAK_FP64 = 78.6e12
+PEAK_SPLIT = 2.5e15 / 6   # FP32 products as six bf16 MFMA products (dense bf16 peak)
 PEAK_HBM = 8.0e12      # B/s
 PMC_COPY_BYTES = 1 << 30      # calibration copy of --pmc-run (read and written once)
 # kernel name prefix (as rocprofv3 reports it) of each H*X stage's FP32 launch
@@ -53,7 +54,8 @@ STAGE_KERNEL = {"radial_inverse": ("k_radial_inverse_mfma<float",),
                 "legendre_analysis": ("k_legendre_analysis<float",
                                       "k_legendre_analysis_fold<float"),
                 "radial_forward": ("k_radial_forward_mfma<float",),
-                "kb_project": ("k_kb_gemm<float",), "kb_apply": ("k_kb_apply_wide<", "k_kb_apply<float")}
+                "kb_project": ("k_kb_gemm_split", "k_kb_gemm<float"),
+                "kb_apply": ("k_kb_apply_split", "k_kb_apply_wide<float", "k_kb_apply<float")}
 
 
 def algorithmic_flops(w, k, n_proj=0):
@@ -803,11 +805,13 @@ def main():
     alg_b = stage_bytes(w, w.k, n_proj, 4)[stage]
     achieved = alg / (avg_ms * 1e-3)
     tr = measured_traffic(STAGE_KERNEL[stage], w.name)
-    # every H*X stage runs its contraction on FP32 MFMA (the phi stage as an
+    # the projector products of this block run on bf16 MFMA (each operand in
+    # three parts), every other H*X stage on FP32 MFMA (the phi stage as an
     # exact Toeplitz + Hankel product, credited at real-FFT flops only)
+    peak = PEAK_SPLIT if stage.startswith("kb_") else PEAK_FP32
     roof = {"bound": "mfma", "achieved": round(achieved / 1e12, 3),
-            "peak": PEAK_FP32 / 1e12, "unit": "TFLOP/s",
-            "frac": round(achieved / PEAK_FP32, 4),
+            "peak": round(peak / 1e12, 1), "unit": "TFLOP/s",
+            "frac": round(achieved / peak, 4),
             "traffic": None if tr is None else round(tr[0]),
             "kernel": tr[1] if tr else STAGE_KERNEL[stage][0], "stage": dom,
             "avg_launch_ms": round(avg_ms, 4), "launches": launches,
@@ -823,6 +827,8 @@ def main():
         if "mfma_flop_f32" in row:
             # MFMA work the kernel executes (counters) over its launch time
             roof["mfma_executed_tflops"] = round(row["mfma_flop_f32"] / (avg_ms * 1e-3) / 1e12, 2)
+    # against the FP32 MFMA peak: the projector products, split over bf16
+    # MFMA, pass 1
     gemm_frac = {st: v["frac_peak"] for st, v in
                  stage_rates(prof, stage_flops(w, w.k, n_proj), PEAK_FP32, "_fp32").items()}
     # counter-based MFMA utilisation of each FP32 stage kernel (committed
