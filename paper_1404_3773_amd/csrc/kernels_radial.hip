@@ -332,29 +332,49 @@ __global__ __launch_bounds__(256) void k_radial_forward_mfma(
       step(c * 4 * CK + 4 * t + kk, ca[t], cb[t]);
     }
   }
+  // epilogue in batches of G column tiles: a batch's operands are loaded with
+  // clamped indices before its first (guarded) store, so they are in flight
+  // together (one at a time behind the guards | batches of 4 tiles in FP32, 2
+  // in FP64 | of 2 and 1, in us with all three operands: 309 atoms, k = 500,
+  // FP32 4650 | 4150 | 3650, k = 250, FP64 4410 | 3330 | 3160; larger batches
+  // cost waves)
+  constexpr int G = sizeof(T) == 4 ? 2 : 1;
 #pragma unroll
   for (int u = 0; u < MT; ++u) {
     const int mt = wave + 4 * u;
     if (mt >= nmt) break;
-    const int n = mt * 16 + l16;
-    if (n >= Nl) continue;
-    const int64_t row = obase + n;
-    const T kin = kinetic ? lamh[static_cast<int64_t>(l) * N + n] - cshift : T(0);
+    const int n = mt * 16 + l16, nc = min(n, Nl - 1);
+    const int64_t row = obase + nc;
+    const T kin = kinetic ? lamh[static_cast<int64_t>(l) * N + nc] - cshift : T(0);
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
+    for (int n0 = 0; n0 < NT; n0 += G) {
+      T zv[G][4], yv[G][4], ov[G][4];
+      auto batch = [&](const T* Y, int64_t ld, T (*y)[4]) __attribute__((always_inline)) {
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        // columns past k (among them any clamped onto valid data) are skipped
-        const int i = i0 + NT * MF<T>::row(lane, v) + nt;
-        if (i >= k) continue;
-        T z = acc[u][nt][v];
-        if (Zkb) z += ZP ? zk[u][nt][v * ZP] : Zkb[static_cast<int64_t>(i) * d + row];
-        if (kinetic)
-          z += kin * (EPR ? yin[u][nt][v * EPR] : Yin[static_cast<int64_t>(i) * ldin + row]);
-        T val = alpha * z;
-        if (beta != T(0))
-          val += beta * (EPR ? yold[u][nt][v * EPR] : Yold[static_cast<int64_t>(i) * ldold + row]);
-        out[static_cast<int64_t>(i) * ldout + row] = static_cast<TO>(val);
+        for (int nt = 0; nt < G; ++nt)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const int i = i0 + NT * MF<T>::row(lane, v) + n0 + nt;
+            y[nt][v] = Y[static_cast<int64_t>(min(i, k - 1)) * ld + row];
+          }
+      };
+      if (!ZP && Zkb) batch(Zkb, d, zv);
+      if (!EPR && kinetic) batch(Yin, ldin, yv);
+      if (!EPR && beta != T(0)) batch(Yold, ldold, ov);
+#pragma unroll
+      for (int nt = 0; nt < G; ++nt) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          T z = acc[u][n0 + nt][v];
+          if (Zkb) z += ZP ? zk[u][n0 + nt][v * ZP] : zv[nt][v];
+          if (kinetic) z += kin * (EPR ? yin[u][n0 + nt][v * EPR] : yv[nt][v]);
+          T val = alpha * z;
+          if (beta != T(0)) val += beta * (EPR ? yold[u][n0 + nt][v * EPR] : ov[nt][v]);
+          // columns past k (among them any clamped onto valid data) are skipped
+          const int i = i0 + NT * MF<T>::row(lane, v) + n0 + nt;
+          if (n < Nl && i < k)
+            out[static_cast<int64_t>(i) * ldout + row] = static_cast<TO>(val);
+        }
       }
     }
   }
@@ -366,20 +386,21 @@ __global__ __launch_bounds__(256) void k_radial_forward_mfma(
 // load every operand fragment at once (ONE: one chunk of CK k-steps); longer
 // ones stream chunks of 1 to kStreamCK k-steps with the next chunk in flight.
 // The streamed forward kernel of a wide block waits on memory more than on the
-// matrix cores (0.56 of the time), so its registers go to waves (5 to 8 per
+// matrix cores (0.56 of the time), so its registers go to waves (4 to 6 per
 // SIMD in FP32, 3 to 5 in FP64, from 3 and 4) and not to longer chunks or
 // epilogue operands loaded ahead, and a workgroup takes 64 columns: the l's
 // table, five times the size of A's 32-column block, is read half as often, A
-// in pieces of 256 bytes or more.  Forward in us, 32 columns and 4 k-steps per
-// chunk | 32 and 1 | 64 and 1 | 64 and 2 (the last three without operands ahead):
-// 147 atoms, k = 400, FP64 1892 | 1698 | 1709 | 1688, FP32 1313 | 1317 | 1153 |
-// 1166; 309 atoms, k = 250, FP64 3013 | 3039 | 3067 | 2749, k = 500, FP32 4072 |
-// 4218 | 3408 | 3357; L = 41, N = 73, 110 nodes, k = 100, FP32 131 | 131 | 116 |
-// 107.  Up to 32 columns FP64 takes 32 and 1 (147 atoms, k = 21: 181 | 171) and
-// FP32, bound by the latency of the few workgroups, stays with 32 and 4 (147
-// atoms, k = 32: 118 | 134), as it does below 2048 workgroups of 64 columns (L
-// = 31, N = 66, 100 nodes, k = 48: 27.8 against 32.0; FP64 there 54 against 50) or
-// where 64-column workgroups pad more than 1/8 (k = 130: 72 against 80).
+// in pieces of 256 bytes or more.  Forward in us (epilogue operands one at a
+// time), 32 columns and 4 k-steps per chunk | 32 and 1 | 64 and 1 | 64 and 2 (the
+// last three without operands ahead): 147 atoms, k = 400, FP64 1892 | 1698 | 1709
+// | 1688, FP32 1313 | 1317 | 1153 | 1166; 309 atoms, k = 250, FP64 3013 | 3039 |
+// 3067 | 2749, k = 500, FP32 4072 | 4218 | 3408 | 3357; L = 41, N = 73, 110 nodes,
+// k = 100, FP32 131 | 131 | 116 | 107.  Up to 32 columns FP64 takes 32 and 1 (147
+// atoms, k = 21: 181 | 171) and FP32, bound by the latency of the few workgroups,
+// stays with 32 and 4 (147 atoms, k = 32: 118 | 134), as it does below 2048
+// workgroups of 64 columns (L = 31, N = 66, 100 nodes, k = 48: 27.8 against 32.0;
+// FP64 there 54 against 50) or where 64-column workgroups pad more than 1/8
+// (k = 130: 72 against 80).
 constexpr int64_t kWideForwardWgs = 2048;
 constexpr int kStreamCK = 4;
 template <typename T, int CK, bool ONE>
@@ -458,8 +479,9 @@ void launch_radial_forward(const Basis& b, const DevTables<T>& tb, const T* A, c
       (sizeof(T) == 8 || static_cast<int64_t>(n64) * b.L * b.L >= kWideForwardWgs))
     return go(std::integral_constant<int, 4>(), std::integral_constant<int, 2>(),
               std::false_type(), std::false_type());
-  go(std::integral_constant<int, RI_NT>(), std::integral_constant<int, sizeof(T) == 8 ? 1 : kStreamCK>(),
-     std::false_type(), std::false_type());
+  go(std::integral_constant<int, RI_NT>(),
+     std::integral_constant<int, sizeof(T) == 8 ? 1 : kStreamCK>(), std::false_type(),
+     std::false_type());
 }
 
 #define CES_INST(T)                                                                           \
