@@ -489,6 +489,7 @@ ces_status h_step_block(Ham& h, const Layout& ly, void* work, int k, const T* Yi
   T* A = Ptr<T>::at(work, ly.A);
   T* C = Ptr<T>::at(work, ly.C);
   const int kp = static_cast<int>(round_up(k, kColPad));
+  const size_t ng = size_t(b.n_r) * b.n_theta * (2 * size_t(b.L) - 1) * kp;   // values of g
   T* Zkb = nullptr;
   if (h.n_proj > 0) {
     // C = diag(h) P^T Yin (n_proj x kp, row-major), then Zkb = P C (d x k)
@@ -497,8 +498,16 @@ ces_status h_step_block(Ham& h, const Layout& ly, void* work, int k, const T* Yi
     const int64_t ldp = sizeof(T) == 8 ? b.d : f32_ld(b.d);   // P row stride
     {
       StageTimer t(stage_id<T>(ST_KB_C), s);
-      launch_kb_gemm<T>(Pd, b.d, ldp, Yin, ldin, hd, C, Ptr<T>::at(work, ly.Cpart), h.n_proj, k,
-                        kp, s);
+      // partial sums from G through g, which nothing uses before the radial
+      // inverse, unless their own region is larger (tiny grids)
+      T* part = Ptr<T>::at(work, ly.Cpart);
+      size_t elems = kb_partial_bytes(h.n_proj, k, b.d) / sizeof(T);
+      const size_t idle = (ly.gbuf - ly.G) / sizeof(T) + ng;
+      if (idle > elems) {
+        part = G;
+        elems = idle;
+      }
+      launch_kb_gemm<T>(Pd, b.d, ldp, Yin, ldin, hd, C, part, elems, h.n_proj, k, kp, s);
     }
     Zkb = Ptr<T>::at(work, ly.Zkb);
     StageTimer t(stage_id<T>(ST_KB_Z), s);
@@ -514,7 +523,7 @@ ces_status h_step_block(Ham& h, const Layout& ly, void* work, int k, const T* Yi
     // one kernel from G to A (timed as the phi stage); a second part of A
     // takes the place of g
     StageTimer t(stage_id<T>(ST_PHI), s);
-    const int parts = fused_parts(b, kp, size_t(b.n_r) * b.n_theta * (2 * size_t(b.L) - 1) * kp);
+    const int parts = fused_parts(b, kp, ng);
     if (parts == 2) A2 = gbuf;
     launch_angular_fused<T>(b, fused_of<T>(b), ab_of<T>(h), G, A, gbuf, parts, kp, s);
   } else {

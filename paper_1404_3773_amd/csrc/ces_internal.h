@@ -140,7 +140,8 @@ ces_status fail(ces_status s, const std::string& msg);   // sets the thread's la
 
 inline size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 
-// Byte offsets of the regions of a caller workspace for k columns.
+// Byte offsets of the regions of a caller workspace for k columns; G, A and
+// gbuf follow each other in this order.
 struct Layout {
   size_t G = 0, A = 0, gbuf = 0, B1 = 0, B2 = 0, V3 = 0, F0 = 0, F1 = 0, C = 0, Cpart = 0,
          Zkb = 0, S1 = 0, S2 = 0, vec = 0, part = 0, info = 0, solver = 0, total = 0;
@@ -258,11 +259,12 @@ void launch_convert(const Tin* src, int64_t lds, Tout* dst, int64_t ldd, int64_t
 inline int64_t f32_ld(int64_t d) { return (d + 31) / 32 * 32; }
 // C[q][i] = h_q sum_alpha P[q][alpha] Y[alpha][i] (projector product; P n_proj x d
 // row-major with row stride ldp, Y column-major d x k, C row-major n_proj x kp
-// with zeros for i >= k); part: kb_partial_bytes(n_proj, k, d) bytes of scratch.
+// with zeros for i >= k); part: part_elems values of scratch, at least
+// kb_partial_bytes(n_proj, k, d) bytes of them (more room, more split-K chunks).
 size_t kb_partial_bytes(int n_proj, int k, int64_t d);
 template <typename T>
 void launch_kb_gemm(const T* P, int64_t d, int64_t ldp, const T* Y, int64_t ldy, const T* h,
-                    T* C, T* part, int n_proj, int k, int kp, hipStream_t s);
+                    T* C, T* part, size_t part_elems, int n_proj, int k, int kp, hipStream_t s);
 // part[c][q][i] (row-major k x kp per chunk c of the rows) = the chunk's share
 // of (A^T B)[q][i] for column-major rows x k blocks A, B, on FP64 MFMA with
 // the projector product's kernel; at most part_cap doubles of part are used.

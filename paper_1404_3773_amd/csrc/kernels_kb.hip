@@ -64,7 +64,8 @@ struct KgVec {
 struct KgWide64 {
   static constexpr int KB = 16, TM = 4, TN = 4;
 };
-constexpr int kKbPerXcd = 64;   // resident workgroups per XCD (32 CUs, 2 each)
+constexpr int kKbPerXcd = 64;      // resident workgroups per XCD (32 CUs, 2 each)
+constexpr int kKbMaxPerXcd = 64;   // split-K chunks per XCD, at most
 
 // LDS row pitch of the staged tiles: the MFMA operand reads take 16 rows x 4
 // consecutive alpha (rows c16, columns kk); with pitch KB + 2 (FP32) the 64
@@ -823,8 +824,8 @@ inline unsigned kb_workgroups(int nchunk, int nM, int nN, bool xcd_chunk) {
 // costs about 1 / 1.5 M of a step).  Few tiles (small blocks or few
 // projectors) take many short chunks, so that every CU has work: 13
 // projectors x 4 columns, d = 162,000: 32 chunks of 158 steps left 7/8 of the
-// chip idle.
-KbGrid kb_grid_for(int BM, int BN, int KB, int slots, int n_proj, int k, int64_t d) {
+// chip idle.  At most `room` chunks, what the partial sums' buffer holds.
+KbGrid kb_grid_for(int BM, int BN, int KB, int slots, int n_proj, int k, int64_t d, int64_t room) {
   KbGrid gr;
   gr.nM = (n_proj + BM - 1) / BM;
   gr.nN = (k + BN - 1) / BN;
@@ -832,9 +833,9 @@ KbGrid kb_grid_for(int BM, int BN, int KB, int slots, int n_proj, int k, int64_t
   const double elems = double(n_proj) * gr.nN * BN;
   int c_best = 1;
   double best = 1e300;
-  for (int c = 1; c <= 64; ++c) {
+  for (int c = 1; c <= kKbMaxPerXcd; ++c) {
     const int64_t per = (steps + 8 * c - 1) / (8 * c);   // steps per chunk
-    if (c > 1 && per < 4) break;
+    if (c > 1 && (per < 4 || 8 * c > room)) break;
     const int64_t rounds = (int64_t(c) * gr.nM * gr.nN + slots - 1) / slots;
     const double cost = double(rounds) * double(per + 4) + 8.0 * c * elems / 1.5e6;
     if (cost < best) {
@@ -842,17 +843,44 @@ KbGrid kb_grid_for(int BM, int BN, int KB, int slots, int n_proj, int k, int64_t
       c_best = c;
     }
   }
-  const int want = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(8 * c_best, steps)));
+  const int64_t want = std::max<int64_t>(1, std::min({int64_t(8) * c_best, steps, room}));
   gr.kchunk = round_up((d + want - 1) / want, KB);
-  gr.nchunk = static_cast<int>((d + gr.kchunk - 1) / gr.kchunk);
+  gr.nchunk = static_cast<int>((d + gr.kchunk - 1) / gr.kchunk);   // <= want
   return gr;
 }
 template <typename S>
-KbGrid kb_grid(int n_proj, int k, int64_t d) {
-  return kb_grid_for(32 * S::TM, 32 * S::TN, S::KB, kKbPerXcd, n_proj, k, d);
+KbGrid kb_grid(int n_proj, int k, int64_t d, int64_t room) {
+  return kb_grid_for(32 * S::TM, 32 * S::TN, S::KB, kKbPerXcd, n_proj, k, d, room);
 }
-KbGrid kb_split_grid(int n_proj, int k, int64_t d) {
-  return kb_grid_for(kSplitM, kSplitN, kSplitK, 32, n_proj, k, d);   // one workgroup per CU
+KbGrid kb_split_grid(int n_proj, int k, int64_t d, int64_t room) {
+  // one workgroup per CU
+  return kb_grid_for(kSplitM, kSplitN, kSplitK, 32, n_proj, k, d, room);
+}
+
+// Chunks the partial sums' own region is sized for: 8 c, c <= 4 such that an
+// XCD's c nM nN workgroups fill whole rounds of kKbPerXcd as nearly as
+// possible, of at least 16 steps.
+template <typename S>
+int64_t kb_region_chunks(int n_proj, int k, int64_t d) {
+  constexpr int KB = S::KB;
+  const int64_t nM = (n_proj + 32 * S::TM - 1) / (32 * S::TM);
+  const int64_t nN = (k + 32 * S::TN - 1) / (32 * S::TN);
+  const int64_t steps = (d + KB - 1) / KB;
+  int c_best = 1;
+  double waste_best = 2.0;
+  for (int c = 1; c <= 4; ++c) {
+    if (c > 1 && steps < int64_t(8 * c) * 16) break;
+    const int64_t wg = c * nM * nN;
+    const int64_t rounds = (wg + kKbPerXcd - 1) / kKbPerXcd;
+    const double waste = double(rounds * kKbPerXcd - wg) / double(rounds * kKbPerXcd);
+    if (waste < waste_best - 1e-9) {
+      waste_best = waste;
+      c_best = c;
+    }
+  }
+  const int64_t want = std::max<int64_t>(1, std::min<int64_t>(8 * c_best, steps));
+  const int64_t kchunk = round_up((d + want - 1) / want, KB);
+  return (d + kchunk - 1) / kchunk;
 }
 
 // FP32 products with at least 96 projectors and more than 128 columns run on
@@ -875,24 +903,22 @@ inline bool kb_wide64(int n_proj, int k, int64_t d) {
 
 }  // namespace
 
-// Split-K partial sums of a product with up to k columns: the chunk count
-// grows as the column count falls, so the largest need over every width <= k
-// (a narrower call, e.g. a Lanczos vector or the last column chunk).
+// The partial sums' own region of a product with up to k columns: the chunk
+// count grows as the column count falls, so the largest need over every width
+// <= k (a narrower call, e.g. a Lanczos vector or the last column chunk).  The
+// grids above ask for up to 512 chunks (1130 MiB at 1236 projectors, k = 1000,
+// against 270 MiB here); a product gets them in a buffer that is idle while it
+// runs, and takes fewer where no buffer is larger than this region.
 size_t kb_partial_bytes(int n_proj, int k, int64_t d) {
   if (n_proj <= 0) return 0;
   size_t most = 0;
   // the grids depend on kc through ceil(kc / 64) at most
   for (int kc = std::min(k, 64);; kc = std::min(kc + 64, k)) {
     const size_t kp = size_t(round_up(kc, kColPad));
-    const size_t c32 = size_t(std::max({kb_grid<KgVec>(n_proj, kc, d).nchunk,
-                                        kb_grid<KbShape<float>>(n_proj, kc, d).nchunk,
-                                        kb_split(n_proj, kc) ? kb_split_grid(n_proj, kc, d).nchunk
-                                                             : 0})) *
+    const size_t c32 = size_t(std::max(kb_region_chunks<KgVec>(n_proj, kc, d),
+                                       kb_region_chunks<KbShape<float>>(n_proj, kc, d))) *
                        sizeof(float);
-    const size_t c64 =
-        size_t(std::max(kb_grid<KbShape<double>>(n_proj, kc, d).nchunk,
-                        kb_wide64(n_proj, kc, d) ? kb_grid<KgWide64>(n_proj, kc, d).nchunk : 0)) *
-        sizeof(double);
+    const size_t c64 = size_t(kb_region_chunks<KbShape<double>>(n_proj, kc, d)) * sizeof(double);
     most = std::max(most, std::max(c32, c64) * size_t(n_proj) * kp);
     if (kc == k) break;
   }
@@ -925,13 +951,14 @@ void allow_lds(K kern, size_t bytes) {
 
 template <typename T>
 void launch_kb_gemm(const T* P, int64_t d, int64_t ldp, const T* Y, int64_t ldy, const T* h,
-                    T* C, T* part, int n_proj, int k, int kp, hipStream_t s) {
+                    T* C, T* part, size_t part_elems, int n_proj, int k, int kp, hipStream_t s) {
+  const int64_t room = static_cast<int64_t>(part_elems / (size_t(n_proj) * kp));
   int nchunk = 0;
   auto go = [&](auto shape, auto db, auto vw) {
     typedef decltype(shape) S;
     constexpr bool DB = decltype(db)::value;
     constexpr int VW = decltype(vw)::value;
-    const KbGrid gr = kb_grid<S>(n_proj, k, d);
+    const KbGrid gr = kb_grid<S>(n_proj, k, d, room);
     const bool xc = gr.nchunk % 8 == 0;
     const unsigned nwg = kb_workgroups(gr.nchunk, gr.nM, gr.nN, xc);
     constexpr size_t lds = kg_lds_bytes<T, S>(DB, VW);
@@ -943,7 +970,7 @@ void launch_kb_gemm(const T* P, int64_t d, int64_t ldp, const T* Y, int64_t ldy,
   if constexpr (sizeof(T) == 4) {
     if (kb_split(n_proj, k) && ldp % 4 == 0 && ldy % 4 == 0 &&
         reinterpret_cast<uintptr_t>(P) % 16 == 0 && reinterpret_cast<uintptr_t>(Y) % 16 == 0) {
-      const KbGrid gr = kb_split_grid(n_proj, k, d);
+      const KbGrid gr = kb_split_grid(n_proj, k, d, room);
       allow_lds(&k_kb_gemm_split, kSplitLds);
       k_kb_gemm_split<<<8 * ((gr.nchunk + 7) / 8) * gr.nM * gr.nN, 512, kSplitLds, s>>>(
           P, d, ldp, Y, ldy, part, n_proj, k, kp, gr.kchunk, gr.nM, gr.nN, gr.nchunk);
@@ -971,14 +998,8 @@ void launch_kb_gemm(const T* P, int64_t d, int64_t ldp, const T* Y, int64_t ldy,
 int launch_atb_partial(const double* A, int64_t lda, const double* B, int64_t ldb, double* part,
                        int64_t part_cap, int64_t rows, int k, int kp, hipStream_t s) {
   // the projector product's split-K grid, with no more chunks than `part` holds
-  KbGrid gr = kb_grid<KbShape<double>>(k, k, rows);
-  const int64_t per_chunk = static_cast<int64_t>(k) * kp;
-  const int64_t maxc = std::max<int64_t>(1, part_cap / per_chunk);
-  if (gr.nchunk > maxc) {
-    constexpr int KB = KbShape<double>::KB;
-    gr.kchunk = round_up((rows + maxc - 1) / maxc, KB);
-    gr.nchunk = static_cast<int>((rows + gr.kchunk - 1) / gr.kchunk);
-  }
+  const KbGrid gr =
+      kb_grid<KbShape<double>>(k, k, rows, part_cap / (static_cast<int64_t>(k) * kp));
   const bool xc = gr.nchunk % 8 == 0;
   const unsigned nwg = kb_workgroups(gr.nchunk, gr.nM, gr.nN, xc);
   auto run = [&](auto vw) {
@@ -1036,8 +1057,9 @@ template void launch_kb_apply<float>(const float*, int64_t, int64_t, const float
 template void launch_kb_apply<double>(const double*, int64_t, int64_t, const double*, double*,
                                       int, int, int, hipStream_t);
 template void launch_kb_gemm<float>(const float*, int64_t, int64_t, const float*, int64_t,
-                                    const float*, float*, float*, int, int, int, hipStream_t);
+                                    const float*, float*, float*, size_t, int, int, int, hipStream_t);
 template void launch_kb_gemm<double>(const double*, int64_t, int64_t, const double*, int64_t,
-                                     const double*, double*, double*, int, int, int, hipStream_t);
+                                     const double*, double*, double*, size_t, int, int, int,
+                                     hipStream_t);
 
 }  // namespace ces
