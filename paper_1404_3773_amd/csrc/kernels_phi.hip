@@ -28,6 +28,7 @@
 
 #include <algorithm>
 #include <type_traits>
+#include <utility>
 
 #include "ces_internal.h"
 #include "mfma.h"
@@ -324,6 +325,137 @@ __global__ __launch_bounds__(256) void k_density(const T* __restrict__ g,
   }
 }
 
+// Density, a row per workgroup: where registers or the number of rows leave
+// the kernel above too few waves (rule at launch_density_phi).  The points are
+// the rows of D (M tiles dealt to the four waves), the slots go through LDS 32
+// columns at a time with the next block in flight, the angle table cos | sin(2
+// pi u / n) lies in LDS and is walked by (m p) mod n; each wave adds its
+// tiles' column sums to an LDS row of rho.
+constexpr int kDensityWorkgroups = 1024;
+constexpr int kDensityNT = 2;
+template <typename T, int LP>
+__global__ __launch_bounds__(256) void k_density_rows(const T* __restrict__ g,
+                                                      const double* __restrict__ occ,
+                                                      double* __restrict__ rho,
+                                                      const double* __restrict__ cs, int L, int kp,
+                                                      int n_phi, int k, int64_t n_rows) {
+  typedef typename MF<T>::acc acc_t;
+  constexpr int GW = 16 * kDensityNT + 1;
+  constexpr int K2 = 2 * LP, KPH = LP / 4;
+  constexpr int GPT = K2 / 8;                   // g values per thread per tile
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  const int S = 2 * L - 1;
+  double* racc = reinterpret_cast<double*>(smem_raw);            // [n_phi]
+  T* ct = reinterpret_cast<T*>(racc + n_phi);                    // [2][n_phi] cos | sin
+  T* gs = ct + 2 * n_phi;                                        // [K2][GW]
+  const int tid = threadIdx.x;
+  const int ii = tid & 31, kr = tid >> 5;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, kk = lane >> 4;
+  const int ncb = (kp + 16 * kDensityNT - 1) / (16 * kDensityNT);
+  const int phalf = n_phi / 2;                  // points 0..phalf are formed
+  const int nMT = (phalf + 1 + 15) / 16;
+  for (int e = tid; e < 2 * n_phi; e += 256) ct[e] = static_cast<T>(cs[e]);
+  // this thread's g rows (slot s < L -> K row s; slot L + j -> row LP + j)
+  int sof[GPT];
+  bool sok[GPT];
+#pragma unroll
+  for (int u = 0; u < GPT; ++u) {
+    const int kx = kr + 8 * u;
+    const bool sn = kx >= LP;
+    const int kl = sn ? kx - LP : kx;
+    sok[u] = sn ? kl < L - 1 : kl < L;
+    sof[u] = sok[u] ? (sn ? L + kl : kl) * kp : 0;
+  }
+  const int64_t rstride = static_cast<int64_t>(S) * kp;
+  const int64_t ntask = n_rows * ncb;
+  T gp[GPT];
+  auto fetch = [&](int64_t task) {
+    const int64_t row = task / ncb;
+    const int cb = static_cast<int>(task - row * ncb);
+    const int col = min(cb * 16 * kDensityNT + ii, kp - 1);
+    const T* gr = g + row * rstride + col;
+#pragma unroll
+    for (int u = 0; u < GPT; ++u) gp[u] = gr[sof[u]];
+  };
+  int64_t task = static_cast<int64_t>(blockIdx.x) * ncb;   // first column block of a row
+  if (task < ntask) fetch(task);
+  for (int64_t row = blockIdx.x; row < n_rows; row += gridDim.x) {
+    for (int e = tid; e < n_phi; e += 256) racc[e] = 0.0;
+    for (int cb = 0; cb < ncb; ++cb) {
+      const int i0 = cb * 16 * kDensityNT;
+      const bool ok_col = i0 + ii < kp;
+#pragma unroll
+      for (int u = 0; u < GPT; ++u) gs[(kr + 8 * u) * GW + ii] = sok[u] && ok_col ? gp[u] : T(0);
+      __syncthreads();   // gs (and, at cb = 0, the zeroed racc and the tables) visible
+      const int64_t next = cb + 1 < ncb ? row * ncb + cb + 1 : (row + gridDim.x) * ncb;
+      if (next < ntask) fetch(next);                  // next tile, in flight
+      // column weights 2 occ_i of this lane's columns (0 past k)
+      double wcol[kDensityNT];
+#pragma unroll
+      for (int nt = 0; nt < kDensityNT; ++nt) {
+        const int i = i0 + nt * 16 + l16;
+        wcol[nt] = i < k ? 2.0 * occ[i] : 0.0;
+      }
+      for (int mt = wave; mt < nMT; mt += 4) {
+        const int p = mt * 16 + l16;
+        const int pc = p <= phalf ? p : 0;            // padded rows: any finite value
+        const int d4 = (4 * pc) % n_phi;
+        acc_t acc[2][kDensityNT];                          // [cos part, sin part]
+#pragma unroll
+        for (int half = 0; half < 2; ++half)
+#pragma unroll
+          for (int nt = 0; nt < kDensityNT; ++nt) acc[half][nt] = zero_acc<acc_t>();
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+          // m = 4t + kk (cos half) or 4t + kk + 1 (sin half): u = (m p) mod n_phi
+          int u = ((kk + half) * pc) % n_phi;
+          const T* tb = ct + half * n_phi;
+          const T* grow = gs + (half * LP + kk) * GW + l16;
+#pragma unroll
+          for (int t = 0; t < KPH; ++t) {
+            const T a = tb[u];
+#pragma unroll
+            for (int nt = 0; nt < kDensityNT; ++nt)
+              acc[half][nt] = MF<T>::mma(a, grow[4 * t * GW + nt * 16], acc[half][nt]);
+            u += d4;
+            u -= u >= n_phi ? n_phi : 0;
+          }
+        }
+        // psi(p) = C + S and psi(n - p) = C - S: weighted squares summed over
+        // this lane's columns, then over the 16 lanes of a row
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          double sp = 0.0, sm = 0.0;
+#pragma unroll
+          for (int nt = 0; nt < kDensityNT; ++nt) {
+            const double c = static_cast<double>(acc[0][nt][v]);
+            const double sn = static_cast<double>(acc[1][nt][v]);
+            const double xp = c + sn, xm = c - sn;
+            sp = fma(wcol[nt] * xp, xp, sp);
+            sm = fma(wcol[nt] * xm, xm, sm);
+          }
+#pragma unroll
+          for (int off = 1; off < 16; off <<= 1) {
+            sp += __shfl_xor(sp, off, 64);
+            sm += __shfl_xor(sm, off, 64);
+          }
+          const int pr = mt * 16 + MF<T>::row(lane, v);
+          if (l16 == 0 && pr <= phalf) {
+            racc[pr] += sp;
+            if (pr > 0 && 2 * pr != n_phi) racc[n_phi - pr] += sm;
+          }
+        }
+      }
+      __syncthreads();   // gs is refilled next; racc complete after the last block
+    }
+    double* out = rho + row * n_phi;
+    for (int e = tid; e < n_phi; e += 256) out[e] = racc[e];
+    __syncthreads();   // racc is zeroed for the next row
+  }
+}
+
 // ------------------------------------------- radial sums of one function
 
 // One function's radial stages, columns = radial nodes.  A workgroup takes 64
@@ -421,23 +553,14 @@ void with_ltiles(int L, F&& f) {
   }
 }
 
-// f(std::integral_constant<int, trig_kt(L)>()): an even count of k-steps
-template <typename F>
+// f(std::integral_constant<int, trig_kt(L)>()): an even count of k-steps, at
+// most MOST
+template <int MOST = 24, int KT = 2, typename F>
 void with_kt(int L, F&& f) {
-  switch (trig_kt(L)) {
-    case 2: f(std::integral_constant<int, 2>()); break;
-    case 4: f(std::integral_constant<int, 4>()); break;
-    case 6: f(std::integral_constant<int, 6>()); break;
-    case 8: f(std::integral_constant<int, 8>()); break;
-    case 10: f(std::integral_constant<int, 10>()); break;
-    case 12: f(std::integral_constant<int, 12>()); break;
-    case 14: f(std::integral_constant<int, 14>()); break;
-    case 16: f(std::integral_constant<int, 16>()); break;
-    case 18: f(std::integral_constant<int, 18>()); break;
-    case 20: f(std::integral_constant<int, 20>()); break;
-    case 22: f(std::integral_constant<int, 22>()); break;
-    default: f(std::integral_constant<int, 24>()); break;
+  if constexpr (KT < MOST) {
+    if (trig_kt(L) > KT) return with_kt<MOST, KT + 2>(L, std::forward<F>(f));
   }
+  f(std::integral_constant<int, KT>());
 }
 
 // One wave per (row, 16 columns), or the four waves of a workgroup on one
@@ -494,13 +617,37 @@ void launch_phi_synthesis_cols(const Basis& b, const double* g, int k, int kp, d
   synthesis_rows(b, g, k, kp, f, ldf, int64_t(b.n_r) * b.n_theta, nullptr, nullptr, 0, s);
 }
 
+// A wave per row, or a workgroup per row where a wave's coefficients of one
+// tile and the next take so many registers that one or two waves are left per
+// SIMD (FP64 from L = 57, FP32 from L = 89), and for several column tiles on
+// few rows.  Density in us, a wave | a workgroup per row: k = 32, n_phi = 4 L,
+// 60 nodes (L >= 88: 30), FP64 L = 55 195 | 242, 57 448 | 259, FP32 L = 88 300 |
+// 307, 89 922 | 309; L = 9, FP64, 432 rows, n_phi = 72, k = 64 20.7 | 17.6,
+// n_phi = 512, k = 64 51.5 | 37.9, k = 16 18.5 | 22.6; 1620 rows, n_phi = 512, k =
+// 64 76.9 | 96.1; L = 16, 1152 rows, n_phi = 64, k = 64 33.4 | 33.8.
+constexpr int64_t kDensityWaveRows = 1024;
 template <typename T>
 void launch_density_phi(const Basis& b, const T* gbuf, const double* occ, double* rho, int k,
                         int kp, hipStream_t s) {
   const int64_t n_rows = int64_t(b.n_r) * b.n_theta;
+  constexpr int KTW = sizeof(T) == 8 ? 14 : 22;     // most k-steps of a half a wave takes
+  if (trig_kt(b.L) > KTW || (kp > 16 && n_rows < kDensityWaveRows)) {
+    const unsigned nb = static_cast<unsigned>(std::min<int64_t>(n_rows, kDensityWorkgroups));
+    return with_ltiles(b.L, [&](auto lt) {
+      constexpr int LP = 16 * decltype(lt)::value;
+      const size_t lds = size_t(b.n_phi) * sizeof(double) + 2 * size_t(b.n_phi) * sizeof(T) +
+                         size_t(2 * LP) * (16 * kDensityNT + 1) * sizeof(T);
+      if (lds > 65536)      // n_phi <= 2048: at most 99 KB
+        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_density_rows<T, LP>),
+                                  hipFuncAttributeMaxDynamicSharedMemorySize,
+                                  static_cast<int>(lds));
+      k_density_rows<T, LP><<<nb, 256, lds, s>>>(gbuf, occ, rho, b.dev_cs, b.L, kp, b.n_phi, k,
+                                                 n_rows);
+    });
+  }
   const T* tb = reinterpret_cast<const T*>(sizeof(T) == 8 ? (const void*)b.dev_trig_s64
                                                           : (const void*)b.dev_trig_s32);
-  with_kt(b.L, [&](auto kt) {
+  with_kt<KTW>(b.L, [&](auto kt) {
     constexpr int KT = decltype(kt)::value;
     const size_t acc = 4 * size_t(b.n_phi) * sizeof(double);
     const size_t tab = size_t(b.n_phi / 32 + 1) * KT * 2 * 64 * sizeof(T);
