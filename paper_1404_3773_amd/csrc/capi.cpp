@@ -1334,6 +1334,23 @@ ces_status ces_chefsi(ces_ham hh, int k, double* d_X, int64_t ldx, int degree, d
   return CES_OK;
 }
 
+namespace {
+// One or two grid functions go one by one through the transforms of a single
+// function (radial nodes as columns): the 16-column tiles of the block
+// transforms are mostly padding.  To the grid and back in us, block | one by
+// one: one function, 60 x 50 x 100 grid (L = 25) 32.6, 39.8 | 14.2, 15.5, 180 x 122
+// x 244 (L = 61) 619, 522 | 68, 63; two on 24 x 18 x 36 (L = 9) 14.6, 14.7 | 28.8,
+// 28.6, 36 x 34 x 68 (L = 17) 17.4, 22.1 | 28.4, 28.6, 60 x 50 x 100 32.8, 39.5 |
+// 28.4, 31.0, 225 x 162 x 324 (L = 81) 1364, 2487 | 263, 430.  A pair back from
+// many more theta nodes than L needs stays a block (the few workgroups of its
+// Legendre analysis have long sums: 24 x 600 x 36, L = 9, 52.6 | 71.5).
+constexpr int64_t kPairRows = 3000;
+bool one_by_one(const Basis& b, int k, int most_theta) {
+  return k == 1 ||
+         (k == 2 && int64_t(b.n_r) * b.n_theta >= kPairRows && b.n_theta <= most_theta);
+}
+}  // namespace
+
 ces_status ces_to_grid(ces_ham hh, int k, const double* d_X, int64_t ldx, double* d_f,
                        void* d_work, size_t work_bytes, void* stream) {
   CES_TRY(check_ham(hh));
@@ -1346,6 +1363,13 @@ ces_status ces_to_grid(ces_ham hh, int k, const double* d_X, int64_t ldx, double
   const Basis& b = *h.basis;
   double* G = Ptr<double>::at(d_work, ly.G);
   double* gbuf = Ptr<double>::at(d_work, ly.gbuf);
+  if (one_by_one(b, k, b.n_theta)) {
+    for (int i = 0; i < k; ++i)
+      launch_inverse_one(b, b.t64.RiT, d_X + i * ldx, G, gbuf, d_f + i * b.n_grid, nullptr, nullptr,
+                         0, s);
+    CES_HIP(hipGetLastError());
+    return CES_OK;
+  }
   for (int64_t c0 = 0; c0 < k; c0 += ly.kc64) {   // column chunks the regions hold
     const int kc = static_cast<int>(std::min<int64_t>(ly.kc64, k - c0));
     const int kp = static_cast<int>(round_up(kc, kColPad));
@@ -1369,6 +1393,12 @@ ces_status ces_from_grid(ces_ham hh, int k, const double* d_f, double* d_X, int6
   const Basis& b = *h.basis;
   double* A = Ptr<double>::at(d_work, ly.A);
   double* gh = Ptr<double>::at(d_work, ly.gbuf);
+  if (one_by_one(b, k, 4 * b.L)) {
+    for (int i = 0; i < k; ++i)
+      launch_forward_one(b, d_f + i * b.n_grid, nullptr, gh, A, d_X + i * ldx, s);
+    CES_HIP(hipGetLastError());
+    return CES_OK;
+  }
   for (int64_t c0 = 0; c0 < k; c0 += ly.kc64) {   // column chunks the regions hold
     const int kc = static_cast<int>(std::min<int64_t>(ly.kc64, k - c0));
     const int kp = static_cast<int>(round_up(kc, kColPad));
