@@ -884,11 +884,18 @@ int64_t kb_region_chunks(int n_proj, int k, int64_t d) {
 }
 
 // FP32 products with at least 96 projectors and more than 128 columns run on
-// the split kernels.  Below, their 256 x 256 tiles are mostly padding (d =
-// 162,000, C and Z = P C in us, FP32 | split: 192 projectors, k = 128: 168, 97
-// | 166, 110; k = 200: 218, 150 | 168, 116; 64 projectors, k = 200: 160, 70 |
-// 158, 54; 512, k = 512: 716, 706 | 411, 467).
-inline bool kb_split(int n_proj, int k) { return n_proj >= 96 && k > 128; }
+// the split kernels when the contraction is long or the product large.  Below,
+// their 256 x 256 tiles are mostly padding (d = 162,000, C and Z = P C in us,
+// FP32 | split: 192 projectors, k = 128: 168, 97 | 166, 110; k = 200: 218, 150 |
+// 168, 116; 64 projectors, k = 200: 160, 70 | 158, 54; 512, k = 512: 716, 706 |
+// 411, 467) or too few: one workgroup per CU, d / 256 x k / 256 of them for Z
+// (H X with k = 256 columns, time of the split kernels over the FP32 ones: 300
+// projectors, d = 972 1.14, 8,000 1.23, 12,500 1.15, 19,220 1.00, 50,430 0.90; 1236
+// projectors, d = 2,023 1.02, 8,000 1.00, 12,500 0.91, 50,430 0.69; over 600 sizes the
+// rule costs 0.5 % more than the faster kernel of each, 15 % at most).
+inline bool kb_split(int n_proj, int k, int64_t d) {
+  return n_proj >= 96 && k > 128 && (d >= 15000 || double(d) * k * n_proj >= 1.5e9);
+}
 
 // FP64 C = P^T Y on 128 x 128 tiles (KgWide64) for long contractions whose
 // columns fill them as well as 64-wide ones (an even number of 64-column
@@ -968,7 +975,7 @@ void launch_kb_gemm(const T* P, int64_t d, int64_t ldp, const T* Y, int64_t ldy,
     nchunk = gr.nchunk;
   };
   if constexpr (sizeof(T) == 4) {
-    if (kb_split(n_proj, k) && ldp % 4 == 0 && ldy % 4 == 0 &&
+    if (kb_split(n_proj, k, d) && ldp % 4 == 0 && ldy % 4 == 0 &&
         reinterpret_cast<uintptr_t>(P) % 16 == 0 && reinterpret_cast<uintptr_t>(Y) % 16 == 0) {
       const KbGrid gr = kb_split_grid(n_proj, k, d, room);
       allow_lds(&k_kb_gemm_split, kSplitLds);
@@ -1020,7 +1027,7 @@ template <typename T>
 void launch_kb_apply(const T* P, int64_t d, int64_t ldp, const T* C, T* Z, int n_proj, int k,
                      int kp, hipStream_t s) {
   if constexpr (sizeof(T) == 4) {
-    if (kb_split(n_proj, k)) {
+    if (kb_split(n_proj, k, d)) {
       const int nI = (k + kSplitM - 1) / kSplitM;
       const int nA = static_cast<int>((d + kSplitN - 1) / kSplitN);
       allow_lds(&k_kb_apply_split, kSplitLds);
