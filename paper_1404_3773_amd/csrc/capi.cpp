@@ -469,6 +469,13 @@ template <>
 const FusedTables<float>& fused_of<float>(const Basis& b) { return b.f32; }
 
 template <typename T>
+const T* v4_of(const Ham& h);
+template <>
+const double* v4_of<double>(const Ham& h) { return h.v4_64; }
+template <>
+const float* v4_of<float>(const Ham& h) { return h.v4_32; }
+
+template <typename T>
 const T* ab_of(const Ham& h);
 template <>
 const double* ab_of<double>(const Ham& h) { return h.ab64; }
@@ -519,13 +526,13 @@ ces_status h_step_block(Ham& h, const Layout& ly, void* work, int k, const T* Yi
     StageTimer t(stage_id<T>(ST_RADIAL_INV), s);
     launch_radial_inverse<T>(b, tb, Yin, ldin, G, k, kp, s);
   }
-  if (b.L <= kFusedL) {
+  if (b.L <= kFusedL && fused_route(b, kp, sizeof(T))) {
     // one kernel from G to A (timed as the phi stage); a second part of A
     // takes the place of g
     StageTimer t(stage_id<T>(ST_PHI), s);
     const int parts = fused_parts(b, kp, ng);
     if (parts == 2) A2 = gbuf;
-    launch_angular_fused<T>(b, fused_of<T>(b), ab_of<T>(h), G, A, gbuf, parts, kp, s);
+    launch_angular_fused<T>(b, fused_of<T>(b), v4_of<T>(h), G, A, gbuf, parts, kp, s);
   } else {
     {
       StageTimer t(stage_id<T>(ST_LEG_SYNTH), s);
@@ -1059,10 +1066,10 @@ ces_status ces_basis_tables(ces_basis bb, double* h_zeros, double* h_radial, dou
 }
 
 namespace {
-// V_eff in the form the angular stage takes (h.ab64, h.ab32).
+// V_eff in the forms the angular stage takes.
 void veff_tables(Ham& h, hipStream_t s) {
   if (h.basis->L <= kFusedL)
-    launch_veff_quadrant(*h.basis, h.veff, h.ab64, h.ab32, s);
+    launch_veff_forms(*h.basis, h.veff, h.v4_64, h.v4_32, h.ab64, h.ab32, s);
   else
     launch_veff_fourier(*h.basis, h.veff, h.ab64, h.ab32, s);
 }
@@ -1084,13 +1091,14 @@ ces_status ces_ham_create(ces_basis bb, const double* d_veff, int n_proj, const 
   h.basis = &b;
   h.n_proj = n_proj;
   const size_t S = 2 * size_t(b.L) - 1;
-  const size_t nab =
-      size_t(b.n_r) * b.n_theta * (b.L <= kFusedL ? 64 : 2 * S);
+  const size_t rows = size_t(b.n_r) * b.n_theta, nab = rows * 2 * S;
+  const size_t nv4 = b.L <= kFusedL ? rows * 64 : 0;
+  const size_t sz_v4 = align256(nv4 * 8) + align256(nv4 * 4);
   const size_t sz_v = align256(size_t(b.n_grid) * 8), sz_ab64 = align256(nab * 8),
                sz_ab32 = align256(nab * 4), sz_p64 = align256(size_t(b.d) * n_proj * 8),
                sz_p32 = align256(size_t(f32_ld(b.d)) * n_proj * 4), sz_h = align256(size_t(n_proj) * 8) + align256(size_t(n_proj) * 4);
   void* blk = nullptr;
-  if (hipMalloc(&blk, sz_v + sz_ab64 + sz_ab32 + sz_p64 + sz_p32 + sz_h) != hipSuccess) {
+  if (hipMalloc(&blk, sz_v + sz_ab64 + sz_ab32 + sz_v4 + sz_p64 + sz_p32 + sz_h) != hipSuccess) {
     delete hh;
     return fail(CES_ERR_ALLOC, "hipMalloc of hamiltonian storage failed");
   }
@@ -1100,6 +1108,11 @@ ces_status ces_ham_create(ces_basis bb, const double* d_veff, int n_proj, const 
   h.ab64 = reinterpret_cast<double*>(p + sz_v);
   h.ab32 = reinterpret_cast<float*>(p + sz_v + sz_ab64);
   char* pp = p + sz_v + sz_ab64 + sz_ab32;
+  if (nv4 > 0) {
+    h.v4_64 = reinterpret_cast<double*>(pp);
+    h.v4_32 = reinterpret_cast<float*>(pp + align256(nv4 * 8));
+  }
+  pp += sz_v4;
   if (n_proj > 0) {
     h.proj64 = reinterpret_cast<double*>(pp);
     h.proj32 = reinterpret_cast<float*>(pp + sz_p64);

@@ -69,7 +69,7 @@ struct Basis {
   float* dev_trig_s32 = nullptr;
   FusedTables<double> f64;         // L <= kFusedL only
   FusedTables<float> f32;
-  double* dev_dir = nullptr;       // V_eff onto the fused stage's phi points
+  double* dev_dir = nullptr;       // V_eff to its two forms (k_veff_forms)
   double* dev_rnode = nullptr;   // [n_r] radial nodes
   double* dev_wr = nullptr;      // [n_r] radial weights (r^2 included)
   double* dev_cth = nullptr;     // [n_theta] cos(theta_j)
@@ -85,10 +85,12 @@ struct Ham {
   Basis* basis = nullptr;
   double* veff = nullptr;   // [n_grid]
   // V_eff as the angular stage takes it: halved phi-Fourier sums
-  // [n_r*n_theta*2*S], or with L <= kFusedL its values on the fused stage's
-  // points [n_r*n_theta][image][point]
+  // [n_r*n_theta*2*S], and with L <= kFusedL also its values on the fused
+  // stage's points [n_r*n_theta][image][point]
   double* ab64 = nullptr;
   float* ab32 = nullptr;
+  double* v4_64 = nullptr;
+  float* v4_32 = nullptr;
   int n_proj = 0;
   double* proj64 = nullptr; // d x n_proj
   float* proj32 = nullptr;
@@ -217,15 +219,16 @@ struct FusedShape {
 FusedShape fused_shape(const Basis& b);
 void fused_tables(const Basis& b, bool f32, std::vector<double>& t12, std::vector<double>& pa,
                   std::vector<double>& pc, std::vector<double>& dir);
-void launch_veff_quadrant(const Basis& b, const double* V, double* v64, float* v32,
-                          hipStream_t s);
+void launch_veff_forms(const Basis& b, const double* V, double* v64, float* v32, double* ab64,
+                       float* ab32, hipStream_t s);
+bool fused_route(const Basis& b, int kp, size_t elem);
 int fused_parts(const Basis& b, int kp, size_t room);
 template <typename T>
 void launch_angular_fused(const Basis& b, const FusedTables<T>& tb, const T* V4, const T* G, T* A0,
                           T* A1, int parts, int kp, hipStream_t s);
 
-// Angular stage on MFMA (L > kFusedL, and the transforms that stop at or
-// start from g): G -> gbuf (n_r x n_theta x S x kp) -> gh (in place)
+// Angular stage on MFMA (L > kFusedL, wide blocks of some smaller L, and the
+// transforms that stop at or start from g): G -> gbuf (n_r x n_theta x S x kp) -> gh (in place)
 // -> A, as three launches.  n_r: radial nodes of the buffers (0: the basis's).
 template <typename T>
 void launch_legendre_synth(const Basis& b, const DevTables<T>& tb, const T* G, T* gbuf, int kp,

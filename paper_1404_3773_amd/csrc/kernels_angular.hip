@@ -923,7 +923,8 @@ void launch_phi_stage(const Basis& b, const T* ab, T* gbuf, int kp, hipStream_t 
       }
     });
   };
-  switch (D.L16) {   // kFusedL < L <= 96 (checked at basis creation)
+  switch (D.L16) {   // L <= 96 (checked at basis creation)
+    case 16: go(std::integral_constant<int, 16>()); break;
     case 32: go(std::integral_constant<int, 32>()); break;
     case 48: go(std::integral_constant<int, 48>()); break;
     case 64: go(std::integral_constant<int, 64>()); break;

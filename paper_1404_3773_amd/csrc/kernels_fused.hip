@@ -230,21 +230,47 @@ __global__ __launch_bounds__(64 * kFusedWaves) void k_angular_fused(
   if (have2) put(m2, a2);
 }
 
-// V4[row][image][p] = (2 pi / n') V_eff(phi') by trigonometric interpolation
-// up to degree 2 (L - 1): a fixed n_phi x 4 NP matrix per basis.
-__global__ __launch_bounds__(256) void k_veff_quadrant(const double* __restrict__ V,
-                                                       const double* __restrict__ W, int n_phi,
-                                                       int nq, double* __restrict__ v64,
-                                                       float* __restrict__ v32, int64_t n_rows) {
-  const int q = threadIdx.x % nq;             // outputs of a row
-  const int64_t row = static_cast<int64_t>(blockIdx.x) * (256 / nq) + threadIdx.x / nq;
-  if (row >= n_rows) return;
-  const double* v = V + row * n_phi;
-  double acc = 0.0;
-#pragma unroll 8
-  for (int p = 0; p < n_phi; ++p) acc = fma(v[p], W[p * nq + q], acc);
-  v64[row * nq + q] = acc;
-  v32[row * nq + q] = static_cast<float>(acc);
+// V_eff in the two forms the angular stage takes for L <= 16, each linear in a
+// row's n_phi values, so one launch of a fixed n_phi x 128 matrix W per basis:
+//   columns 0 .. 63   V4[row][image][p] = (2 pi / n') V_eff(phi'), by
+//                     trigonometric interpolation up to degree 2 (L - 1)
+//   column 64 + q     the phi stage's halved Fourier sums (q < S cosine, then
+//                     sine; kernels.hip), scaled by `scale`
+// A wave owns two rows, a lane one of 64 columns.  Replacing the potential is
+// bound by launches: 10.4 us on a 24 x 18 x 36 grid, as with the sums alone (10.5;
+// 13.8 with a launch for each form).
+constexpr int kVeffCols = 128;
+__global__ __launch_bounds__(256) void k_veff_forms(const double* __restrict__ V,
+                                                    const double* __restrict__ W, int n_phi,
+                                                    int S2, double scale, double* __restrict__ v64,
+                                                    float* __restrict__ v32,
+                                                    double* __restrict__ ab64,
+                                                    float* __restrict__ ab32, int64_t n_rows) {
+  const int q = blockIdx.y * 64 + (threadIdx.x & 63);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t r0 = static_cast<int64_t>(blockIdx.x) * 8 + 2 * wave;
+  if (r0 >= n_rows || q >= 64 + S2) return;
+  const double* va = V + r0 * n_phi;
+  const double* vb = V + min(r0 + 1, n_rows - 1) * n_phi;
+  const double* w = W + q;
+  double a = 0.0, b = 0.0;
+#pragma unroll 16
+  for (int p = 0; p < n_phi; ++p) {
+    const double t = w[p * kVeffCols];
+    a = fma(va[p], t, a);
+    b = fma(vb[p], t, b);
+  }
+  auto put = [&](int64_t row, double x) __attribute__((always_inline)) {
+    if (q < 64) {
+      v64[row * 64 + q] = x;
+      v32[row * 64 + q] = static_cast<float>(x);
+    } else {
+      ab64[row * S2 + q - 64] = scale * x;
+      ab32[row * S2 + q - 64] = static_cast<float>(scale * x);
+    }
+  };
+  put(r0, a);
+  if (r0 + 1 < n_rows) put(r0 + 1, b);
 }
 
 }  // namespace
@@ -310,8 +336,7 @@ void fused_tables(const Basis& b, bool f32, std::vector<double>& t12, std::vecto
       }
   }
   // V4 = (2 pi / n') (1 / n_phi) sum_p V_p [1 + 2 sum_{q <= 2L-2} cos q (phi' - phi_p)]
-  const int nq = 64;
-  dir.assign(size_t(b.n_phi) * nq, 0.0);
+  dir.assign(size_t(b.n_phi) * kVeffCols, 0.0);
   // angles as integer multiples of pi / (n' n_phi); the sum in closed form,
   // sin((2L - 3/2) x) / sin(x / 2)
   const int64_t M = int64_t(n4) * b.n_phi;
@@ -325,17 +350,53 @@ void fused_tables(const Basis& b, bool f32, std::vector<double>& t12, std::vecto
         const long double num = sinl(pi * (long double)(c * x % (4 * M)) / (2 * M));
         const long double sum =
             x == 0 ? (long double)c : num / sinl(pi * (long double)x / (2 * M));
-        dir[size_t(q) * nq + img * 16 + p] = static_cast<double>(2 * pi / n4 / b.n_phi * sum);
+        dir[size_t(q) * kVeffCols + img * 16 + p] = static_cast<double>(2 * pi / n4 / b.n_phi * sum);
       }
+    }
+  const int S = 2 * L - 1;
+  for (int p = 0; p < b.n_phi; ++p)
+    for (int q = 0; q < S; ++q) {
+      const double x = 2.0 * M_PI * (int64_t(q) * p % b.n_phi) / b.n_phi;
+      dir[size_t(p) * kVeffCols + 64 + q] = std::cos(x);
+      dir[size_t(p) * kVeffCols + 64 + S + q] = std::sin(x);
     }
 }
 
-void launch_veff_quadrant(const Basis& b, const double* V, double* v64, float* v32,
-                          hipStream_t s) {
-  const int nq = 64;
+void launch_veff_forms(const Basis& b, const double* V, double* v64, float* v32, double* ab64,
+                       float* ab32, hipStream_t s) {
   const int64_t rows = int64_t(b.n_r) * b.n_theta;
-  k_veff_quadrant<<<static_cast<unsigned>((rows * nq + 255) / 256), 256, 0, s>>>(
-      V, b.dev_dir, b.n_phi, nq, v64, v32, rows);
+  k_veff_forms<<<dim3(static_cast<unsigned>((rows + 7) / 8), 2), 256, 0, s>>>(
+      V, b.dev_dir, b.n_phi, 2 * (2 * b.L - 1), M_PI / b.n_phi, v64, v32, ab64, ab32, rows);
+}
+
+// Whether an H*X of kp columns takes the fused kernel (L <= kFusedL).  It
+// saves two launches and g's three further crossings of memory, and pays with
+// workgroups that run at their slowest wave: per 16 theta rows or fewer, eight
+// waves take ceil(L / 2) pairs of m and the rows in rounds of eight, so few
+// L and row counts fill them (L = 9: 5 of 8 waves, then 9 rows in two rounds).
+// Narrow blocks (work = workgroups times rounds) are bound by launches: fused.
+// Wide ones are fused where the waves are full enough, L = 6 .. 8 and from 11
+// (FP64) or 12 (FP32), in FP32 with L <= 8 always, and on grids with many more
+// theta nodes than L needs where g no longer fits the last-level cache.  H X in
+// us, three kernels | fused, FP64 and FP32: L = 9, 24 x 18 grid, k = 48 24.3 | 18.0,
+// 28.5 | 19.3, k = 512 66 | 63, 51 | 48, k = 1500 143 | 157, 100 | 119; 45 x 18, k = 373
+// 79 | 91, 60 | 72; L = 16, 36 x 32, k = 800 328 | 227, 178 | 166.  Over 570 sizes a
+// precision the rule costs 0.4 % (FP64) and 0.2 % (FP32) more than the faster
+// form of each, and none is over 2 % slower than with three kernels alone;
+// always fused: 1.6 and 2.3 %, at worst 51 and 36 %.
+bool fused_route(const Basis& b, int kp, size_t elem) {
+  const FusedShape f = fused_shape(b);
+  const bool f32 = elem == 4;
+  const int64_t wgs = int64_t(b.n_r) * (kp / 16);
+  const int64_t work = wgs * f.ngrp * ((f.th + kFusedWaves - 1) / kFusedWaves);
+  const bool usual = 2 * b.n_theta <= 5 * b.L;      // theta nodes as L needs them
+  const int narrow = f32 || b.L <= 8 ? 3072 : 2048;
+  if (b.L <= 8) return f32 || work <= narrow || (usual && b.L >= 6);
+  if (!usual) {
+    const size_t g = size_t(b.n_r) * b.n_theta * (2 * b.L - 1) * kp * elem;
+    return wgs <= 256 || (b.L >= 12 && g > size_t(180) * 1000 * 1000);
+  }
+  return work <= narrow || b.L >= (f32 ? 12 : 11);
 }
 
 // Parts of A the fused launch writes: two (each half of the theta groups)
