@@ -396,12 +396,18 @@ __global__ __launch_bounds__(256) void k_radial_forward_mfma(
 // | 1688, FP32 1313 | 1317 | 1153 | 1166; 309 atoms, k = 250, FP64 3013 | 3039 |
 // 3067 | 2749, k = 500, FP32 4072 | 4218 | 3408 | 3357; L = 41, N = 73, 110 nodes,
 // k = 100, FP32 131 | 131 | 116 | 107.  Up to 32 columns FP64 takes 32 and 1 (147
-// atoms, k = 21: 181 | 171) and FP32, bound by the latency of the few workgroups,
-// stays with 32 and 4 (147 atoms, k = 32: 118 | 134), as it does below 2048
-// workgroups of 64 columns (L = 31, N = 66, 100 nodes, k = 48: 27.8 against 32.0;
-// FP64 there 54 against 50) or where 64-column workgroups pad more than 1/8
-// (k = 130: 72 against 80).
-constexpr int64_t kWideForwardWgs = 2048;
+// atoms, k = 21: 181 | 171) and FP32 stays with 32 and 4 (147 atoms, k = 32: 118 |
+// 134).  Few workgroups are bound by the latency of their chunks, one after the
+// other, and take 32 and 4: FP32 below 2048 workgroups of 64 columns (L = 31, N =
+// 66, 100 nodes, k = 48: 27.8 against 32.0), FP64 below 800 of them and 1024 of 32
+// columns (whole H X, 64 and 2 | 32 and 4, N = 150, 225 nodes: L = 5, k = 64 83 | 69,
+// L = 9 113 | 99, L = 17 230 | 213, L = 25 0.946 | 0.947 of the time before either at k =
+// 33, L = 31 0.926 | 0.948; 32 and 1 | 32 and 4: L = 9, k = 32 1.06, L = 20 1.01, L = 31
+// 1.02 times), as does what 64-column workgroups would pad by more than 1/8 (k =
+// 130: 72 against 80).
+template <typename T>
+constexpr int64_t kWideForwardWgs = sizeof(T) == 4 ? 2048 : 800;
+constexpr int64_t kShortChunkWgs = 1024;
 constexpr int kStreamCK = 4;
 template <typename T, int CK, bool ONE>
 void radial_inverse_ck(const Basis& b, const DevTables<T>& tb, const T* X, int64_t ldx, T* G,
@@ -475,13 +481,14 @@ void launch_radial_forward(const Basis& b, const DevTables<T>& tb, const T* A, c
   if (ks <= 16) return one(std::integral_constant<int, 16>());
   if (ks <= 24) return one(std::integral_constant<int, 24>());
   const int n32 = (k + 31) / 32, n64 = (k + 63) / 64;
-  if (n32 > 1 && 16 * n64 <= 9 * n32 &&
-      (sizeof(T) == 8 || static_cast<int64_t>(n64) * b.L * b.L >= kWideForwardWgs))
+  const int64_t lm = int64_t(b.L) * b.L;
+  if (n32 > 1 && 16 * n64 <= 9 * n32 && n64 * lm >= kWideForwardWgs<T>)
     return go(std::integral_constant<int, 4>(), std::integral_constant<int, 2>(),
               std::false_type(), std::false_type());
-  go(std::integral_constant<int, RI_NT>(),
-     std::integral_constant<int, sizeof(T) == 8 ? 1 : kStreamCK>(), std::false_type(),
-     std::false_type());
+  const std::integral_constant<int, RI_NT> nt;
+  if (sizeof(T) == 8 && n32 * lm >= kShortChunkWgs)
+    return go(nt, std::integral_constant<int, 1>(), std::false_type(), std::false_type());
+  go(nt, std::integral_constant<int, kStreamCK>(), std::false_type(), std::false_type());
 }
 
 #define CES_INST(T)                                                                           \
