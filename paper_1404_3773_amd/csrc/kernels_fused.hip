@@ -376,14 +376,15 @@ void launch_veff_forms(const Basis& b, const double* V, double* v64, float* v32,
 // L and row counts fill them (L = 9: 5 of 8 waves, then 9 rows in two rounds).
 // Narrow blocks (work = workgroups times rounds) are bound by launches: fused.
 // Wide ones are fused where the waves are full enough, L = 6 .. 8 and from 11
-// (FP64) or 12 (FP32), in FP32 with L <= 8 always, and on grids with many more
-// theta nodes than L needs where g no longer fits the last-level cache.  H X in
-// us, three kernels | fused, FP64 and FP32: L = 9, 24 x 18 grid, k = 48 24.3 | 18.0,
-// 28.5 | 19.3, k = 512 66 | 63, 51 | 48, k = 1500 143 | 157, 100 | 119; 45 x 18, k = 373
-// 79 | 91, 60 | 72; L = 16, 36 x 32, k = 800 328 | 227, 178 | 166.  Over 570 sizes a
-// precision the rule costs 0.4 % (FP64) and 0.2 % (FP32) more than the faster
-// form of each, and none is over 2 % slower than with three kernels alone;
-// always fused: 1.6 and 2.3 %, at worst 51 and 36 %.
+// (FP64) or 12 (FP32), in FP32 from L = 5 to 8 always, and on grids with many
+// more theta nodes than L needs where g no longer fits the last-level cache;
+// with L <= 4 a workgroup's fixed steps soon outweigh it.  H X in us, three
+// kernels | fused, FP64 and FP32: L = 9, 24 x 18 grid, k = 48 23.2 | 17.9, 24.3 |
+// 19.1, k = 512 67 | 63, 51 | 48, k = 1500 143 | 157, 99 | 119; 45 x 18, k = 373 79 | 91,
+// 60 | 72; L = 16, 36 x 32, k = 800 328 | 227, 180 | 166; L = 1, 90 x 2, k = 100 / 500, FP64
+// 22.9 | 22.6 / 29 | 50, FP32 k = 500 26 | 31; L = 4, 90 x 8, k = 500 69 | 80.  For L >= 4, over
+// 570 sizes a precision the rule costs 0.4 % (FP64) and 0.2 % (FP32) more than the
+// faster form of each; always fused: 1.6 and 2.3 %, at worst 51 and 36 %.
 bool fused_route(const Basis& b, int kp, size_t elem) {
   const FusedShape f = fused_shape(b);
   const bool f32 = elem == 4;
@@ -391,6 +392,7 @@ bool fused_route(const Basis& b, int kp, size_t elem) {
   const int64_t work = wgs * f.ngrp * ((f.th + kFusedWaves - 1) / kFusedWaves);
   const bool usual = 2 * b.n_theta <= 5 * b.L;      // theta nodes as L needs them
   const int narrow = f32 || b.L <= 8 ? 3072 : 2048;
+  if (b.L <= 4) return work <= (512 + 64 * b.L * b.L) * (f32 ? 4 : 1);
   if (b.L <= 8) return f32 || work <= narrow || (usual && b.L >= 6);
   if (!usual) {
     const size_t g = size_t(b.n_r) * b.n_theta * (2 * b.L - 1) * kp * elem;

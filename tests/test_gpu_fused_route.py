@@ -20,7 +20,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("L,N,n_r,n_th,n_ph,k", [
-    (9, 3, 24, 18, 36, 336), (9, 3, 24, 18, 36, 337), (9, 3, 24, 18, 35, 512), (9, 3, 24, 18, 36, 513), (1, 3, 1, 1, 1, 2000), (1, 2, 16, 9, 40, 1700),
+    (9, 3, 24, 18, 36, 336), (9, 3, 24, 18, 36, 337), (9, 3, 24, 18, 35, 512), (9, 3, 24, 18, 36, 513), (1, 3, 1, 1, 1, 2000), (1, 2, 16, 9, 40, 1700), (1, 2, 36, 2, 4, 256),
+    (1, 2, 36, 2, 4, 257), (3, 2, 100, 6, 12, 180),
     (5, 3, 60, 10, 20, 1000), (6, 2, 60, 12, 24, 1000), (7, 2, 12, 30, 29, 1100),
     (10, 2, 30, 40, 40, 128), (10, 2, 30, 40, 40, 160), (11, 2, 40, 23, 44, 400),
     (12, 2, 40, 25, 50, 350), (16, 2, 30, 64, 33, 144), (16, 2, 40, 32, 64, 300)])
