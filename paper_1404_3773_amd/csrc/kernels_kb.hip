@@ -525,8 +525,9 @@ void k_kb_apply_wide(const T* __restrict__ P, int64_t d, int64_t ldp, const T* _
 
 // ------------------------------------------- FP32 products on bf16 MFMA
 //
-// An FP32 value is the exact sum of three bf16 values, x = h + m + l (each the
-// rounding of what the former leave: 8 significant bits each, 24 in all), so
+// An FP32 value of magnitude 2^-110 to 3.39e38 is the exact sum of three bf16
+// values, x = h + m + l (each the rounding of what the former leave: 8
+// significant bits each, 24 in all), so
 // x y = hh' + (hm' + mh') + (hl' + mm' + lh') up to the dropped ml', lm' and
 // ll' terms, which stay below 2^-24 |x y|: one FP32 rounding of the product.
 // The six products run on bf16 MFMA with FP32 accumulators.  A 16x16x32 bf16
@@ -534,9 +535,15 @@ void k_kb_apply_wide(const T* __restrict__ P, int64_t d, int64_t ldp, const T* _
 // register-only loops), so the six cost 0.37 of the FP32 MFMAs, and a K = 32
 // step rounds each accumulator 6 times instead of 8.  Against 64 bits the
 // results are no further off than the FP32 kernels' (H X of the 309-atom shape
-// below, relative 2-norm: 6.6e-8 against 9.1e-8).  The split keeps FP32's exponent range; values above the
-// largest bf16 (3.39e38) round to infinity, and an infinite or NaN input
-// makes the outputs of its row or column NaN.
+// below, relative 2-norm: 6.6e-8 against 9.1e-8).  Below 2^-110 the last bits of
+// x fall under bf16's smallest subnormal (2^-133; conversions and MFMA keep
+// subnormals): at most 2^-134 of each value is lost, so a sum of n products with
+// a y of magnitude one is off by up to n 2^-134 more (d = 16,000, 130 projectors
+// whose term is the output's size, error of H X in units of its maximum: 1.4e-7
+// for blocks of order 2^90 to 2^-110, 2.0e-7 at 2^-114, 2.7e-6 at 2^-118).  Values above
+// the largest bf16 (3.39e38) round to infinity, and an infinite or NaN input
+// makes the outputs of its row or column NaN; H X of a column with an infinity
+// is NaN throughout in either form, the other columns are untouched.
 //
 // Workgroup: 256 x 256 outputs, 8 waves of 64 x 128 (128 accumulators per
 // lane, two waves per SIMD), K in steps of 32 staged in one LDS buffer (98
