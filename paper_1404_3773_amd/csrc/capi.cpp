@@ -245,11 +245,12 @@ ces_status ensure_device(Basis& b) {
       }
     }
   // fused angular stage (FP32 tables rounded from their FP64 values)
-  std::vector<double> ft, fa, fc, ft32, fa32, fc32, dir, dir32;
+  std::vector<double> ft, fa, fc, ft32, fa32, fc32, dir;
   std::vector<float> gt, ga, gc;
   if (b.L <= kFusedL) {
-    fused_tables(b, false, ft, fa, fc, dir);
-    fused_tables(b, true, ft32, fa32, fc32, dir32);
+    fused_tables(b, false, ft, fa, fc);
+    fused_tables(b, true, ft32, fa32, fc32);
+    veff_matrix(b, dir);
     gt.assign(ft32.begin(), ft32.end());
     ga.assign(fa32.begin(), fa32.end());
     gc.assign(fc32.begin(), fc32.end());

@@ -218,7 +218,8 @@ struct FusedShape {
 };
 FusedShape fused_shape(const Basis& b);
 void fused_tables(const Basis& b, bool f32, std::vector<double>& t12, std::vector<double>& pa,
-                  std::vector<double>& pc, std::vector<double>& dir);
+                  std::vector<double>& pc);
+void veff_matrix(const Basis& b, std::vector<double>& dir);
 void launch_veff_forms(const Basis& b, const double* V, double* v64, float* v32, double* ab64,
                        float* ab32, hipStream_t s);
 bool fused_route(const Basis& b, int kp, size_t elem);

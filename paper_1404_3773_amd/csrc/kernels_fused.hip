@@ -35,6 +35,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <numeric>
 #include <type_traits>
 
 #include "ces_internal.h"
@@ -289,17 +290,19 @@ FusedShape fused_shape(const Basis& b) {
 // Operand tables in FP64 (layouts above); the row of D that a lane's register
 // v holds differs between FP64 and FP32, so T2 does too (f32).
 void fused_tables(const Basis& b, bool f32, std::vector<double>& t12, std::vector<double>& pa,
-                  std::vector<double>& pc, std::vector<double>& dir) {
+                  std::vector<double>& pc) {
   const FusedShape f = fused_shape(b);
   const int L = b.L, LP = L * (L + 1) / 2, n4 = 4 * L;
   // cos / sin(m (p + 1/2) 2 pi / n') = trig(m (2 p + 1) 2 pi / (2 n')), rounded
   // once (from long double: an argument of pi times a fraction rounded to FP64
   // is off by up to 4e-16 before the cosine)
-  const long double pi = acosl(-1.0L);
-  auto trig = [&](int sn, int64_t m, int64_t p2) {
-    const long double x = pi * (long double)(m * p2 % (2 * n4)) / n4;
-    return static_cast<double>(sn ? sinl(x) : cosl(x));
-  };
+  std::vector<double> cs[2];
+  for (int u = 0; u < 2 * n4; ++u) {
+    const long double x = acosl(-1.0L) * u / n4;
+    cs[0].push_back(static_cast<double>(cosl(x)));
+    cs[1].push_back(static_cast<double>(sinl(x)));
+  }
+  auto trig = [&](int sn, int m, int p2) { return cs[sn][m * p2 % (2 * n4)]; };
   auto entry = [&](int cls, int kap, int p) -> double {   // classes ce co se so
     const int m = 2 * kap + (cls & 1);
     if (m >= L || p >= L || (cls >= 2 && m == 0)) return 0.0;
@@ -335,30 +338,49 @@ void fused_tables(const Basis& b, bool f32, std::vector<double>& t12, std::vecto
         }
       }
   }
-  // V4 = (2 pi / n') (1 / n_phi) sum_p V_p [1 + 2 sum_{q <= 2L-2} cos q (phi' - phi_p)]
+}
+
+// W of k_veff_forms.  Columns 0 .. 63: V4 = (2 pi / n') (1 / n_phi) sum_p V_p
+// [1 + 2 sum_{q <= 2L-2} cos q (phi' - phi_p)], the sum in closed form, sin((2L -
+// 3/2) x) / sin(x / 2).  The differences are integer multiples x of pi / (n'
+// n_phi), all of them multiples of gcd(n_phi, 2 n'), and each is evaluated once,
+// in long double (first Hamiltonian of a basis, L = 16, n_phi = 64: 2.7 ms with
+// every entry evaluated, for either precision, 0.8 so).
+void veff_matrix(const Basis& b, std::vector<double>& dir) {
+  const int L = b.L, n4 = 4 * L;
+  const long double pi = acosl(-1.0L);
   dir.assign(size_t(b.n_phi) * kVeffCols, 0.0);
-  // angles as integer multiples of pi / (n' n_phi); the sum in closed form,
-  // sin((2L - 3/2) x) / sin(x / 2)
-  const int64_t M = int64_t(n4) * b.n_phi;
+  const int64_t M = int64_t(n4) * b.n_phi, g = std::gcd(b.n_phi, 2 * n4);
+  std::vector<double> known(size_t(2 * M / g), NAN);
+  auto weight = [&](int64_t x) {      // 0 <= x < 2 M
+    double& w = known[x / g];
+    if (std::isnan(w)) {
+      const int64_t c = 4 * L - 3;
+      const long double num = sinl(pi * (long double)(c * x % (4 * M)) / (2 * M));
+      const long double sum = x == 0 ? (long double)c : num / sinl(pi * (long double)x / (2 * M));
+      w = static_cast<double>(2 * pi / n4 / b.n_phi * sum);
+    }
+    return w;
+  };
   for (int img = 0; img < 4; ++img)
     for (int p = 0; p < L; ++p) {
       const int64_t up = (2 * p + 1) * int64_t(b.n_phi);
       const int64_t ph = img == 0 ? up : img == 1 ? M - up : img == 2 ? M + up : 2 * M - up;
-      for (int q = 0; q < b.n_phi; ++q) {
-        const int64_t x = ((ph - 2 * int64_t(n4) * q) % (2 * M) + 2 * M) % (2 * M);
-        const int64_t c = 4 * L - 3;
-        const long double num = sinl(pi * (long double)(c * x % (4 * M)) / (2 * M));
-        const long double sum =
-            x == 0 ? (long double)c : num / sinl(pi * (long double)x / (2 * M));
-        dir[size_t(q) * kVeffCols + img * 16 + p] = static_cast<double>(2 * pi / n4 / b.n_phi * sum);
-      }
+      for (int q = 0; q < b.n_phi; ++q)
+        dir[size_t(q) * kVeffCols + img * 16 + p] =
+            weight(((ph - 2 * int64_t(n4) * q) % (2 * M) + 2 * M) % (2 * M));
     }
   const int S = 2 * L - 1;
+  std::vector<double> cs[2];
+  for (int u = 0; u < b.n_phi; ++u) {
+    cs[0].push_back(std::cos(2.0 * M_PI * u / b.n_phi));
+    cs[1].push_back(std::sin(2.0 * M_PI * u / b.n_phi));
+  }
   for (int p = 0; p < b.n_phi; ++p)
     for (int q = 0; q < S; ++q) {
-      const double x = 2.0 * M_PI * (int64_t(q) * p % b.n_phi) / b.n_phi;
-      dir[size_t(p) * kVeffCols + 64 + q] = std::cos(x);
-      dir[size_t(p) * kVeffCols + 64 + S + q] = std::sin(x);
+      const int u = static_cast<int>(int64_t(q) * p % b.n_phi);
+      dir[size_t(p) * kVeffCols + 64 + q] = cs[0][u];
+      dir[size_t(p) * kVeffCols + 64 + S + q] = cs[1][u];
     }
 }
 

@@ -908,9 +908,13 @@ inline bool kb_split(int n_proj, int k, int64_t d) {
 // columns fill them as well as 64-wide ones (an even number of 64-column
 // tiles).  C in us, 128 x 64 | 128 x 128 tiles: d = 984,150, 1236 projectors,
 // k = 250: 11,620 | 10,440; d = 162,000, k = 256: 192 projectors 382 | 372, 512
-// 751 | 731; k = 400 (7 tiles against 4): 300 projectors 971 | 1132; below d =
-// 100,000 the shorter chunks' starts outweigh it (d = 12,000, 256 projectors,
-// k = 256: 46 | 52).
+// 751 | 731; k = 400 (7 tiles against 4): 300 projectors 971 | 1132.  Below d =
+// 100,000 the shorter chunks' starts outweigh it more often than not (d =
+// 12,000, 256 projectors, k = 256: 46 | 52; whole H X on small grids, time of the wide tiles
+// over the others: d = 33,620, k = 256, 96 projectors 1.03, 700 1.09, 1236 0.97; d =
+// 57,132, 300 projectors, k = 128 1.21, k = 256 0.98, 1236, k = 500 0.99).  The
+// 309-atom product fetches 74.8 GB with it against 65.0 (P and Y once: 17.6):
+// its chunks share less in an XCD's L2, and it is bound by the matrix cores.
 inline bool kb_wide64(int n_proj, int k, int64_t d) {
   return d >= 100000 && n_proj >= 96 && (k + 63) / 64 % 2 == 0;
 }
