@@ -528,7 +528,9 @@ ces_status ces_cluster_quad_loss(int n_clusters, int max_atoms, const int64_t* d
  * (eq. Ar_lm), 4 radial quadrature with the kinetic / projector / Chebyshev
  * epilogue (eq. Arlm_to_coeff), 5 projector product C = diag(h) P^T Y,
  * 6 projector product P C; ids 7..13 are the same stages in FP64 (0..6 are
- * FP32).  ces_profile_enable(1, n) starts
+ * FP32).  Where one kernel takes stages 1 to 3 (L <= 16, narrow blocks and some
+ * wide ones) its time counts as stage 2 and 1 and 3 have no launches.
+ * ces_profile_enable(1, n) starts
  * recording into a pool of n event pairs (launches beyond the pool are not
  * recorded) and clears the totals; ces_profile_enable(0, 0) stops and frees
  * the pool.  Process-wide, not thread-safe; meant for benchmarking. */
