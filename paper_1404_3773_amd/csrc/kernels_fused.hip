@@ -308,14 +308,14 @@ void fused_tables(const Basis& b, bool f32, std::vector<double>& t12, std::vecto
     if (m >= L || p >= L || (cls >= 2 && m == 0)) return 0.0;
     return trig(cls >= 2, m, 2 * p + 1);
   };
-  // the analysis side of an FP32 product makes up for the rounding of the
-  // synthesis side, c^2 / fl(c) instead of c: the few distinct values of a small
-  // L otherwise scale whole slots alike, by up to 5.7e-8 (3.3e-8 so).  Error of
+  // L <= 8: the analysis side of an FP32 product makes up for the rounding of
+  // the synthesis side, c^2 / fl(c) instead of c: their few distinct values
+  // otherwise scale whole slots alike, by up to 5.7e-8 (3.3e-8 so).  Error of
   // the mixed H X of the oscillator, N = 12, against 64 bits in units of the
   // three kernels' (relative 2-norm), c | c^2 / fl(c): L = 4 1.10 | 1.03, L = 8 1.06 |
-  // 1.035, L = 12 0.98 | 0.99; with wells 0.98 to 1.01 either way.
+  // 1.035; with wells 1.00 either way, from L = 9 0.98 to 1.00 with c.
   auto back = [&](double c) {
-    return f32 && c != 0.0 ? c * c / static_cast<double>(static_cast<float>(c)) : c;
+    return f32 && L <= 8 && c != 0.0 ? c * c / static_cast<double>(static_cast<float>(c)) : c;
   };
   const int n1 = 4 * f.kc * 64;
   t12.assign(n1 + kQuadT2, 0.0);
