@@ -84,8 +84,9 @@ void with_nts(bool on, F&& f) {
 // group per wave), 16 NT columns i of one radial node r.
 // g[r][j][s][i] = sum_l Pm[m][l][j] G[r][lm][i].  A wave loads the G fragments
 // of a k-step once for all its JT theta tiles.
-// KS > 0 (L <= 4 KS): every operand of the K loop is loaded before the first
-// MFMA; KS = 0: the K loop streams its operands.
+// Every operand of the K loop (L <= 32: at most KS = 8 k-steps) is loaded before
+// the first MFMA.  (Written without JT, which is one, the loads come in another
+// order: 0.4 % of H X at L = 21.)
 template <typename T, int LS_NT, int KS, int JT>
 __global__ __launch_bounds__(256) void k_legendre_synth(const T* __restrict__ Pm,
                                                         const T* __restrict__ G,
@@ -120,79 +121,30 @@ __global__ __launch_bounds__(256) void k_legendre_synth(const T* __restrict__ Pm
   int col[LS_NT];
 #pragma unroll
   for (int nt = 0; nt < LS_NT; ++nt) col[nt] = min(nt * 16, D.kp - i0 - 16);
-  if constexpr (KS > 0) {
-    const int ks = (K + 3) >> 2;
-    T a[KS][JT], b[KS][LS_NT];
-    // up to 8 k-steps the loops exit early; longer ones take uniform guards
-    // instead, which keeps them unrolled (an early exit there leaves a rolled
-    // loop indexing the operand arrays through scratch)
+  const int ks = (K + 3) >> 2;
+  T a[KS][JT], b[KS][LS_NT];
 #pragma unroll
-    for (int t = 0; t < KS; ++t) {
-      if (KS <= 8 && t >= ks) break;
-      if (t < ks) {
-        // rows l >= L read row L - 1 and are masked where used
-        const int lc = min(m + 4 * t + kk, D.L - 1);
+  for (int t = 0; t < KS; ++t) {
+    if (t >= ks) break;
+    // rows l >= L read row L - 1 and are masked where used
+    const int lc = min(m + 4 * t + kk, D.L - 1);
 #pragma unroll
-        for (int u = 0; u < JT; ++u) a[t][u] = Pa[u][lc * D.J64];
-        const int off = (lc * lc + lc + sgn * m) * D.kp;
-#pragma unroll
-        for (int nt = 0; nt < LS_NT; ++nt) b[t][nt] = Gr[off + col[nt]];
-      }
-    }
-    __builtin_amdgcn_sched_barrier(0);   // every load issued before the first MFMA
-#pragma unroll
-    for (int t = 0; t < KS; ++t) {
-      if (KS <= 8 && t >= ks) break;
-      if (t < ks) {
-        const bool ok = m + 4 * t + kk < D.L;
-#pragma unroll
-        for (int u = 0; u < JT; ++u) {
-          const T av = ok ? a[t][u] : T(0);
-#pragma unroll
-          for (int nt = 0; nt < LS_NT; ++nt) acc[u][nt] = MF<T>::mma(av, b[t][nt], acc[u][nt]);
-        }
-      }
-    }
-  } else {
-  // steps whose four l rows are all below L: row offset (l^2 + l + sgn m) kp
-  // advanced by second differences (l grows by 4 per step)
-  const int nfull = K >> 2;
-  {
-    const int l = m + kk;
-    int64_t off = static_cast<int64_t>(l * l + l + sgn * m) * D.kp;
-    int64_t dof = static_cast<int64_t>(8 * l + 20) * D.kp;
-    const int64_t ddof = 32 * static_cast<int64_t>(D.kp);
-    int64_t pofs = static_cast<int64_t>(l) * D.J64;
-#pragma unroll 4
-    for (int t = 0; t < nfull; ++t) {
-      T a[JT], b[LS_NT];
-#pragma unroll
-      for (int u = 0; u < JT; ++u) a[u] = Pa[u][pofs];
-#pragma unroll
-      for (int nt = 0; nt < LS_NT; ++nt) b[nt] = Gr[off + col[nt]];
-#pragma unroll
-      for (int u = 0; u < JT; ++u)
-#pragma unroll
-        for (int nt = 0; nt < LS_NT; ++nt) acc[u][nt] = MF<T>::mma(a[u], b[nt], acc[u][nt]);
-      pofs += 4 * D.J64;
-      off += dof;
-      dof += ddof;
-    }
-  }
-  if (K & 3) {
-    const int l = m + 4 * nfull + kk;
-    const int lc = min(l, D.L - 1);
+    for (int u = 0; u < JT; ++u) a[t][u] = Pa[u][lc * D.J64];
     const int off = (lc * lc + lc + sgn * m) * D.kp;
-    T b[LS_NT];
 #pragma unroll
-    for (int nt = 0; nt < LS_NT; ++nt) b[nt] = Gr[off + col[nt]];
+    for (int nt = 0; nt < LS_NT; ++nt) b[t][nt] = Gr[off + col[nt]];
+  }
+  __builtin_amdgcn_sched_barrier(0);   // every load issued before the first MFMA
+#pragma unroll
+  for (int t = 0; t < KS; ++t) {
+    if (t >= ks) break;
+    const bool ok = m + 4 * t + kk < D.L;
 #pragma unroll
     for (int u = 0; u < JT; ++u) {
-      const T a = Pa[u][l * D.J64];                 // zero rows for l >= L
+      const T av = ok ? a[t][u] : T(0);
 #pragma unroll
-      for (int nt = 0; nt < LS_NT; ++nt) acc[u][nt] = MF<T>::mma(a, b[nt], acc[u][nt]);
+      for (int nt = 0; nt < LS_NT; ++nt) acc[u][nt] = MF<T>::mma(av, b[t][nt], acc[u][nt]);
     }
-  }
   }
   T* gr = g + (static_cast<int64_t>(r) * D.n_theta * D.S + s) * D.kp + i0 + l16;
 #pragma unroll
@@ -840,47 +792,15 @@ void launch_legendre_synth(const Basis& b, const DevTables<T>& tb, const T* G, T
     return go(std::integral_constant<int, 2>(), (kp + 31) / 32);
   }
   // two column tiles when the block is narrow (no idle MFMA columns), else four
-  // (K loops of up to 8 k-steps, L <= 32, load all their operands at once;
-  // up to 16 (L <= 64) in FP32, where the registers allow it)
-  // In FP32 with 32 < L <= 64, wide blocks (four column tiles) take up to four
-  // 64-row theta groups per workgroup, so each G fragment is read once per
-  // wave for all of them (measured faster there; slower in FP64 and for the
-  // streamed K loop, where the g stores rather than the G reads bound it).
-  const int ngrp = (b.n_theta + 63) / 64;
-  auto go = [&](auto nt_tag, auto jt_tag, int n_ic) {
-    constexpr int NT = decltype(nt_tag)::value, JT = decltype(jt_tag)::value;
-    dim3 grid(n_r * n_ic, (ngrp + JT - 1) / JT, D.S);
-    if constexpr (JT > 1) {
-      k_legendre_synth<T, NT, 16, JT><<<grid, 256, 0, s>>>(tb.Pm, G, gbuf, D, n_ic);
-    } else {
-      if (b.L <= 32) {
-        k_legendre_synth<T, NT, 8, 1><<<grid, 256, 0, s>>>(tb.Pm, G, gbuf, D, n_ic);
-        return;
-      }
-      if constexpr (sizeof(T) == 4) {
-        if (b.L <= 64) {
-          k_legendre_synth<T, NT, 16, 1><<<grid, 256, 0, s>>>(tb.Pm, G, gbuf, D, n_ic);
-          return;
-        }
-      }
-      k_legendre_synth<T, NT, 0, 1><<<grid, 256, 0, s>>>(tb.Pm, G, gbuf, D, n_ic);
-    }
+  auto go = [&](auto nt_tag, int n_ic) {
+    constexpr int NT = decltype(nt_tag)::value;
+    const dim3 grid(n_r * n_ic, (b.n_theta + 63) / 64, D.S);
+    k_legendre_synth<T, NT, 8, 1><<<grid, 256, 0, s>>>(tb.Pm, G, gbuf, D, n_ic);
   };
-  using I = std::integral_constant<int, 1>;
-  if (kp <= 32) return go(std::integral_constant<int, 2>(), I(), (kp + 31) / 32);
-  const int n_ic = (kp + 63) / 64;
-  std::integral_constant<int, 4> nt4;
-  if constexpr (sizeof(T) == 4) {
-    if (b.L > 32 && b.L <= 64) {
-      switch (std::min(ngrp, 4)) {
-        case 1: return go(nt4, I(), n_ic);
-        case 2: return go(nt4, std::integral_constant<int, 2>(), n_ic);
-        case 3: return go(nt4, std::integral_constant<int, 3>(), n_ic);
-        default: return go(nt4, std::integral_constant<int, 4>(), n_ic);
-      }
-    }
-  }
-  go(nt4, I(), n_ic);
+  if (kp <= 32)
+    go(std::integral_constant<int, 2>(), (kp + 31) / 32);
+  else
+    go(std::integral_constant<int, 4>(), (kp + 63) / 64);
 }
 
 template <typename T>
@@ -967,17 +887,11 @@ void launch_legendre_analysis(const Basis& b, const DevTables<T>& tb, const T* g
       go(std::integral_constant<int, 2>());
     return;
   }
-  // l-tiles per slot cover L; theta chunks sized to the registers left
-  if (b.L <= 32) {
-    if (b.n_theta <= 64)
-      k_legendre_analysis<T, 2, 16, true><<<grid, 256, 0, s>>>(tb.PwT, gbuf, A, D, n_ic);
-    else
-      k_legendre_analysis<T, 2, 8, false><<<grid, 256, 0, s>>>(tb.PwT, gbuf, A, D, n_ic);
-  } else if (b.L <= 64) {
-    k_legendre_analysis<T, 4, f32 ? 8 : 4, false><<<grid, 256, 0, s>>>(tb.PwT, gbuf, A, D, n_ic);
-  } else {   // L <= 96
-    k_legendre_analysis<T, 6, f32 ? 4 : 2, false><<<grid, 256, 0, s>>>(tb.PwT, gbuf, A, D, n_ic);
-  }
+  // two l-tiles per slot cover L; theta chunks sized to the registers left
+  if (b.n_theta <= 64)
+    k_legendre_analysis<T, 2, 16, true><<<grid, 256, 0, s>>>(tb.PwT, gbuf, A, D, n_ic);
+  else
+    k_legendre_analysis<T, 2, 8, false><<<grid, 256, 0, s>>>(tb.PwT, gbuf, A, D, n_ic);
 }
 
 #define CES_INST(T)                                                                          \
