@@ -486,8 +486,10 @@ void launch_radial_forward(const Basis& b, const DevTables<T>& tb, const T* A, c
     return go(std::integral_constant<int, 4>(), std::integral_constant<int, 2>(),
               std::false_type(), std::false_type());
   const std::integral_constant<int, RI_NT> nt;
-  if (sizeof(T) == 8 && n32 * lm >= kShortChunkWgs)
-    return go(nt, std::integral_constant<int, 1>(), std::false_type(), std::false_type());
+  if constexpr (sizeof(T) == 8) {
+    if (n32 * lm >= kShortChunkWgs)
+      return go(nt, std::integral_constant<int, 1>(), std::false_type(), std::false_type());
+  }
   go(nt, std::integral_constant<int, kStreamCK>(), std::false_type(), std::false_type());
 }
 
