@@ -506,12 +506,18 @@ ces_status h_step_block(Ham& h, const Layout& ly, void* work, int k, const T* Yi
     const int64_t ldp = sizeof(T) == 8 ? b.d : f32_ld(b.d);   // P row stride
     {
       StageTimer t(stage_id<T>(ST_KB_C), s);
-      // partial sums from G through g, which nothing uses before the radial
-      // inverse, unless their own region is larger (tiny grids)
+      // partial sums in g, which nothing uses before the angular stage, when it
+      // holds all that the chunk model may ask for, else from G through g
+      // (nothing uses G and A before the radial inverse either), unless their
+      // own region is larger (tiny grids).  In G, which the radial inverse
+      // writes right after, H X takes 0.7 % more (L = 25, 40 projectors, k = 64).
       T* part = Ptr<T>::at(work, ly.Cpart);
       size_t elems = kb_partial_bytes(h.n_proj, k, b.d) / sizeof(T);
       const size_t idle = (ly.gbuf - ly.G) / sizeof(T) + ng;
-      if (idle > elems) {
+      if (ng >= size_t(kKbMaxChunks) * h.n_proj * kp) {
+        part = Ptr<T>::at(work, ly.gbuf);
+        elems = ng;
+      } else if (idle > elems) {
         part = G;
         elems = idle;
       }

@@ -265,6 +265,7 @@ inline int64_t f32_ld(int64_t d) { return (d + 31) / 32 * 32; }
 // row-major with row stride ldp, Y column-major d x k, C row-major n_proj x kp
 // with zeros for i >= k); part: part_elems values of scratch, at least
 // kb_partial_bytes(n_proj, k, d) bytes of them (more room, more split-K chunks).
+constexpr int kKbMaxChunks = 512;   // split-K chunks a product may ask for
 size_t kb_partial_bytes(int n_proj, int k, int64_t d);
 template <typename T>
 void launch_kb_gemm(const T* P, int64_t d, int64_t ldp, const T* Y, int64_t ldy, const T* h,

@@ -65,7 +65,7 @@ struct KgWide64 {
   static constexpr int KB = 16, TM = 4, TN = 4;
 };
 constexpr int kKbPerXcd = 64;      // resident workgroups per XCD (32 CUs, 2 each)
-constexpr int kKbMaxPerXcd = 64;   // split-K chunks per XCD, at most
+constexpr int kKbMaxPerXcd = kKbMaxChunks / 8;   // split-K chunks per XCD, at most
 
 // LDS row pitch of the staged tiles: the MFMA operand reads take 16 rows x 4
 // consecutive alpha (rows c16, columns kk); with pitch KB + 2 (FP32) the 64
